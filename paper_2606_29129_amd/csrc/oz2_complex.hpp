@@ -62,8 +62,9 @@ __global__ __launch_bounds__(256) void k1_partials_strided_cplx(
     const double a = norm_entry<RESC>((double)z.x), b = norm_entry<RESC>((double)z.y);
     s = ru_add(s, ru_square(a));
     s = ru_add(s, ru_square(b));
-    mx = fmax(mx, fmax(fabs(a), fabs(b)));
+    if (pmax) mx = fmax(mx, fmax(fabs(a), fabs(b)));
   };
+  round_up_begin();
   if (len == KH) {
 #pragma unroll
     for (int b = 0; b < KH; b += 8) {
@@ -76,6 +77,7 @@ __global__ __launch_bounds__(256) void k1_partials_strided_cplx(
   } else {
     for (int64_t h = 0; h < len; ++h) add(p[h * ld]);
   }
+  round_up_end(s);
   part[c * nvec + v] = s;
   if (pmax) pmax[c * nvec + v] = mx;
 }

@@ -58,6 +58,7 @@ __device__ __forceinline__ void k1_partials_strided_body(
   const int64_t len = k - h0 < kKC ? k - h0 : kKC;
   const T* p = X + v + h0 * ld;
   double s = 0.0, mx = 0.0;
+  round_up_begin();
   if (len == kKC) {
 #pragma unroll
     for (int b = 0; b < kKC; b += 16) {
@@ -67,8 +68,10 @@ __device__ __forceinline__ void k1_partials_strided_body(
         a[i] = norm_entry<RESC>(NT ? (double)__builtin_nontemporal_load(p + (int64_t)(b + i) * ld)
                                    : (double)p[(int64_t)(b + i) * ld]);
       s = ru_add_squares(s, a);
+      if (pmax) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) mx = fmax(mx, fabs(a[i]));
+        for (int i = 0; i < 16; ++i) mx = fmax(mx, fabs(a[i]));
+      }
     }
   } else {
     for (int64_t h = 0; h < len; ++h) {
@@ -77,6 +80,7 @@ __device__ __forceinline__ void k1_partials_strided_body(
       mx = fmax(mx, fabs(a));
     }
   }
+  round_up_end(s);
   part[c * nvec + v] = s;
   if (pmax) pmax[c * nvec + v] = mx;
 }
@@ -107,6 +111,7 @@ __device__ __forceinline__ void k1_partials_contig_body(
   const int64_t len = k - h0 < kKC ? k - h0 : kKC;
   const T* p = X + v * ld + h0;
   double s = 0.0, mx = 0.0;
+  round_up_begin();
   if (len == kKC) {
 #pragma unroll
     for (int b = 0; b < kKC; b += 16) {
@@ -114,8 +119,10 @@ __device__ __forceinline__ void k1_partials_contig_body(
 #pragma unroll
       for (int i = 0; i < 16; ++i) a[i] = norm_entry<RESC>((double)p[b + i]);
       s = ru_add_squares(s, a);
+      if (pmax) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) mx = fmax(mx, fabs(a[i]));
+        for (int i = 0; i < 16; ++i) mx = fmax(mx, fabs(a[i]));
+      }
     }
   } else {
     for (int64_t h = 0; h < len; ++h) {
@@ -124,6 +131,7 @@ __device__ __forceinline__ void k1_partials_contig_body(
       mx = fmax(mx, fabs(a));
     }
   }
+  round_up_end(s);
   part[c * nvec + v] = s;
   if (pmax) pmax[c * nvec + v] = mx;
 }
@@ -150,6 +158,7 @@ __device__ __forceinline__ void fold_chunks(const double* __restrict__ part,
                                             int64_t nvec, int64_t v, double* S_out, double* mx_out) {
   double S = 0.0, mx = 0.0;
   int64_t c = 0;
+  round_up_begin();
   for (; c + 16 <= nchunks; c += 16) {
     double b[16], q[16];
 #pragma unroll
@@ -168,6 +177,7 @@ __device__ __forceinline__ void fold_chunks(const double* __restrict__ part,
     S = ru_add(S, part[c * nvec + v]);
     if (pmax) mx = fmax(mx, pmax[c * nvec + v]);
   }
+  round_up_end(S);
   *S_out = S;
   *mx_out = mx;
 }

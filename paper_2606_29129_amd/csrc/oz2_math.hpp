@@ -1,9 +1,9 @@
 // oz2_math.hpp -- scalar arithmetic of the scaling step (host and device).
 //
-// Everything here is exact or directed-rounded by construction, built from
-// round-to-nearest binary64 operations plus error-free transforms, so that
-// the GPU reproduces the rounded-up squared norms and the scale exponents of
-// Algorithms 1 and 2 bit for bit.  Compile with -ffp-contract=off: every
+// Everything here is exact or directed-rounded by construction, so that the
+// GPU reproduces the rounded-up squared norms (the hardware's own rounding
+// toward +infinity) and the scale exponents of Algorithms 1 and 2
+// (round-to-nearest operations) bit for bit.  Compile with -ffp-contract=off: every
 // fused multiply-add is written explicitly.
 #pragma once
 
@@ -100,60 +100,50 @@ OZ2_HD float rd_f32(double d) {
   return f;
 }
 
-// RU(x*x) for x = 0 or x >= 2^-480: the FMA residual fma(x, x, -p) is then
-// exact.  An infinite or NaN square passes through (its residual is not
-// positive).
-OZ2_HD double ru_square_normal(double x) {
-  const double p = x * x;
-  return fma(x, x, -p) > 0.0 ? next_up_nonneg(p) : p;
+// Rounded-up binary64 sums of squares, by the hardware's directed rounding:
+// between round_up_begin and round_up_end the wave's binary64 rounding mode
+// (MODE bits 3:2) is toward +infinity, so one multiply is RU(a a) and one add
+// RU(s + q), subnormals and overflow to +inf included -- against about 25
+// operations per entry, most of them one dependent chain, for the same values
+// from round-to-nearest operations and their exact errors.  The operations
+// are volatile asm, which keeps them in order between the two mode switches;
+// round_up_end takes the sum so that what is computed from it (in
+// round-to-nearest) stays behind the switch back.
+__device__ __forceinline__ void round_up_begin() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 2, 2), 1");
+#endif
 }
-
-// RU(a*a) in binary64.  Below |a| = 2^-480 the residual would not be exact,
-// so the square is formed on a*2^600 and scaled back, rounding up once more
-// (rounding up onto a coarser grid after rounding up onto a finer one that
-// contains it is one rounding up).
-OZ2_HD double ru_square(double a) {
-  const double x = a < 0 ? -a : a;
-  if (x < 0x1p-480 && x != 0.0) {
-    double b = ldexp(x, 600);              // exact, b < 2^120
-    double pb = b * b;                     // >= 2^-948: residual exact
-    double eb = fma(b, b, -pb);
-    if (eb > 0.0) pb = next_up_nonneg(pb);
-    double r = ldexp(pb, -1200);           // one correctly rounded scaling
-    if (ldexp(r, 1200) < pb) r = next_up_nonneg(r);  // scaling back is exact
-    return r;
-  }
-  return ru_square_normal(x);
+__device__ __forceinline__ void round_up_end(double& s) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 2, 2), 0" : "+v"(s));
+#endif
 }
-
-// RU(x + y) for x, y >= 0: the rounded sum, raised by one ulp when the exact
-// error (TwoSum) is positive.  An infinite or NaN sum passes through (its
-// error is NaN).
-OZ2_HD double ru_add(double x, double y) {
-  const double s = x + y;
-  const double bb = s - x;
-  const double err = (x - (s - bb)) + (y - bb);
-  return err > 0.0 ? next_up_nonneg(s) : s;
+__device__ __forceinline__ double ru_square(double a) {
+  double r = 0.0;
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("v_mul_f64 %0, %1, %1" : "=v"(r) : "v"(a));
+#endif
+  return r;
 }
-
-// s + a_0^2 + ... + a_{NA-1}^2 with every square and every addition rounded
-// up, in that order.  The group is screened once for tiny entries
-// (0 < |a| < 2^-480, which take ru_square's scaled path); a group without
-// any runs as straight-line code.
+__device__ __forceinline__ double ru_add(double x, double y) {
+  double r = 0.0;
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("v_add_f64 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
+#endif
+  return r;
+}
+// s + a_0^2 + ... + a_{NA-1}^2, every square and every addition rounded up,
+// in that order; each square is formed behind the addition before it, so that
+// the chain of additions is not held up.
 template <int NA>
-OZ2_HD double ru_add_squares(double s, const double (&a)[NA]) {
-  bool tiny = false;
+__device__ __forceinline__ double ru_add_squares(double s, const double (&a)[NA]) {
+  double q = ru_square(a[0]);
 #pragma unroll
   for (int i = 0; i < NA; ++i) {
-    const double x = a[i] < 0 ? -a[i] : a[i];
-    tiny = tiny || (x < 0x1p-480 && x != 0.0);
-  }
-  if (tiny) {
-#pragma unroll
-    for (int i = 0; i < NA; ++i) s = ru_add(s, ru_square(a[i]));
-  } else {
-#pragma unroll
-    for (int i = 0; i < NA; ++i) s = ru_add(s, ru_square_normal(a[i] < 0 ? -a[i] : a[i]));
+    const double qi = q;
+    s = ru_add(s, qi);
+    if (i + 1 < NA) q = ru_square(a[i + 1]);
   }
   return s;
 }
