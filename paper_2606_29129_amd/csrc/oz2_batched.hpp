@@ -11,6 +11,7 @@
 // dealt out round-robin to the workgroups.
 #pragma once
 
+#include "oz2_k12_scale.hpp"
 #include "oz2_k1_norm.hpp"
 #include "oz2_k2_split.hpp"
 #include "oz2_k3_gemm.hpp"
@@ -79,8 +80,12 @@ constexpr int kBatchBK = 128;
 // The fast modes need at most 2 limbs of 40 bits for |a'| (< 2^79 at N = 20).
 constexpr int kBatchLimbs = 2;
 
-// Stages with a per-problem block count.
-enum BatchStage { kB_K1A = 0, kB_K1B, kB_FOLDA, kB_FOLDB, kB_K2A, kB_K2B, kB_K4, kB_NSTAGES };
+// Stages with a per-problem block count.  A problem with k <= kK12MaxK has
+// blocks in the K12 stages (norms, exponents and conversion in one), a longer
+// one in the separate stages of the three steps.
+enum BatchStage {
+  kB_K12A = 0, kB_K12B, kB_K1A, kB_K1B, kB_FOLDA, kB_FOLDB, kB_K2A, kB_K2B, kB_K4, kB_NSTAGES
+};
 
 // Block b of a stage (b counted from the stage's first block) finds its
 // problem in a host-built table (one load) and its position inside the
@@ -169,6 +174,30 @@ __global__ __launch_bounds__(256, 3) void kb_stage_pair(const BatchProb* __restr
     kb_stage_body<S1>(probs, prefix, owner, batch, status, b);
   else
     kb_stage_body<S2>(probs, prefix, owner + nfirst, batch, status, b - nfirst);
+}
+
+// Norms, exponents and conversion of the problems with k <= kK12MaxK, rows
+// of A and columns of B in one launch.
+__global__ __launch_bounds__(64 * kK12Waves, 4) void kb_k12(
+    const BatchProb* __restrict__ probs, const int64_t* __restrict__ prefix,
+    const uint16_t* __restrict__ owner, int batch, int64_t nfirst, int* __restrict__ status) {
+  const int64_t b = blockIdx.x;
+  const int p = owner[b];
+  const BatchProbDev& P = reinterpret_cast<const BatchProbDev*>(probs)[p];
+  const ModTable* tab = (const ModTable*)P.tab;
+  const K12Shape sh = k12_shape<kK12VL<double>>(P.Kp);
+  if (b < nfirst) {
+    const int64_t* pre = prefix + (int64_t)kB_K12A * (batch + 1);
+    k12_scale_body<double, false, true, kBatchLimbs, false>((const double*)P.A, P.lda, P.m, P.k, P.mode, tab, P.N,
+                                        (int32_t*)P.eA, (double*)P.SA, status, (int8_t*)P.RA,
+                                        P.Mp, P.Kp, sh, (int)(b - pre[p]), (int)(pre[p + 1] - pre[p]));
+  } else {
+    const int64_t* pre = prefix + (int64_t)kB_K12B * (batch + 1);
+    k12_scale_body<double, true, true, kBatchLimbs, false>((const double*)P.B, P.ldb, P.n, P.k, P.mode, tab, P.N,
+                                       (int32_t*)P.eB, (double*)P.SB, status, (int8_t*)P.RB,
+                                       P.Np, P.Kp, sh, (int)(b - nfirst - pre[p]),
+                                       (int)(pre[p + 1] - pre[p]));
+  }
 }
 
 // Work item: problem, plane, tile row, tile column (16 bits each).

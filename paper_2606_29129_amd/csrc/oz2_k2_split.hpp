@@ -35,11 +35,10 @@ struct Limbs {
   double x[LIMBS];
 };
 
+// The limbs of an integer-valued v.
 template <int LIMBS>
-OZ2_HD Limbs<LIMBS> make_limbs(double a, int32_t e) {
+OZ2_HD Limbs<LIMBS> limbs_of(double v) {
   Limbs<LIMBS> L;
-  double v = (e == kExpNonFinite) ? 0.0 : trunc(ldexp(a, e));
-  if (!(v == v)) v = 0.0;  // NaN entries of a flagged row give 0
 #pragma unroll
   for (int j = LIMBS - 1; j >= 1; --j) {
     const double scale = ldexp(1.0, kLimbBits * j);
@@ -49,6 +48,13 @@ OZ2_HD Limbs<LIMBS> make_limbs(double a, int32_t e) {
   }
   L.x[0] = v;
   return L;
+}
+
+template <int LIMBS>
+OZ2_HD Limbs<LIMBS> make_limbs(double a, int32_t e) {
+  double v = (e == kExpNonFinite) ? 0.0 : trunc(ldexp(a, e));
+  if (!(v == v)) v = 0.0;  // NaN entries of a flagged row give 0
+  return limbs_of<LIMBS>(v);
 }
 
 template <int LIMBS>

@@ -216,6 +216,8 @@ OZ2_HD double crt_unscale(const double (&acc)[S], const ModTable& T, int32_t E) 
 // in general, four for small outputs.)  The results go through a per-wave
 // LDS tile so that each store instruction writes column segments of
 // 32 / WPB entries.
+// status (may be null): OZ2_STATUS_NONFINITE is set by an output of a flagged
+// row or column, where no earlier kernel could set it.
 constexpr int kK4WavesPerBlock = 2;
 constexpr int kK4WavesPerBlockSmall = 4;
 
@@ -223,7 +225,8 @@ template <int S, typename TO, int WPB = kK4WavesPerBlock>
 __device__ __forceinline__ void k4_crt_body(
     const uint8_t* __restrict__ U, const int32_t* __restrict__ eA,
     const int32_t* __restrict__ eB, const ModTable* __restrict__ tab, int N,
-    int64_t m, int64_t n, int64_t Mp, int64_t Np, TO* __restrict__ C, int64_t ldc, int64_t bx) {
+    int64_t m, int64_t n, int64_t Mp, int64_t Np, TO* __restrict__ C, int64_t ldc, int64_t bx,
+    int* __restrict__ status = nullptr) {
   static_assert(WPB == 2 || WPB == 4, "waves per block");
   constexpr int RPW = 32 / WPB;             // rows of the block per wave
   __shared__ TO tile[4][RPW][33];
@@ -305,6 +308,7 @@ __device__ __forceinline__ void k4_crt_body(
       const int32_t e = er[r];
       if (e == kExpNonFinite || f == kExpNonFinite) {
         v = __builtin_nan("");
+        if (status) atomicOr(status, 1);
       } else {
         double a[S];
 #pragma unroll
@@ -334,8 +338,9 @@ template <int S, typename TO, int WPB = kK4WavesPerBlock>
 __global__ __launch_bounds__(256) void k4_crt(
     const uint8_t* __restrict__ U, const int32_t* __restrict__ eA,
     const int32_t* __restrict__ eB, const ModTable* __restrict__ tab, int N,
-    int64_t m, int64_t n, int64_t Mp, int64_t Np, TO* __restrict__ C, int64_t ldc) {
-  k4_crt_body<S, TO, WPB>(U, eA, eB, tab, N, m, n, Mp, Np, C, ldc, blockIdx.x);
+    int64_t m, int64_t n, int64_t Mp, int64_t Np, TO* __restrict__ C, int64_t ldc,
+    int* __restrict__ status) {
+  k4_crt_body<S, TO, WPB>(U, eA, eB, tab, N, m, n, Mp, Np, C, ldc, blockIdx.x, status);
 }
 
 // C = 0 (k = 0).

@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "ozaki2.h"
+#include "oz2_k12_scale.hpp"
 #include "oz2_k1_norm.hpp"
 #include "oz2_k2_split.hpp"
 #include "oz2_k3_gemm.hpp"
@@ -320,6 +321,30 @@ void launch_split(const T* A, int64_t lda, const T* B, int64_t ldb, int64_t m, i
       (const int32_t*)(ws + L.eB), (int8_t*)(ws + L.RB), L.Np, k, tab, N, L.Kp, gAx, nA);
 }
 
+// K12 for both operands.  A debug call runs no K4, so its status bit is set
+// by this kernel (behind a launch that clears it).
+template <typename T>
+void launch_k12(const T* A, int64_t lda, const T* B, int64_t ldb, int64_t m, int64_t n, int64_t k,
+                const Layout& L, char* ws, const ModTable* tab, int N, int mode, bool dbg) {
+  int* status = (int*)(ws + L.status);
+  if (dbg) k_clear_status<<<1, 64, 0, g_stream>>>(status);
+  constexpr int VL = kK12VL<T>;
+  K12Shape sh = k12_shape<VL>(L.Kp);
+  auto blocks = [&] { return k12_blocks(m, VL, sh) + k12_blocks(n, VL, sh); };
+  auto go = [&](auto kernel) {
+    kernel<<<(unsigned)blocks(), 64 * kK12Waves, 0, g_stream>>>(
+        A, lda, m, B, ldb, n, k, mode, tab, N, (int32_t*)(ws + L.eA), (int32_t*)(ws + L.eB),
+        (double*)(ws + L.SA), (double*)(ws + L.SB), (int8_t*)(ws + L.RA), (int8_t*)(ws + L.RB),
+        L.Mp, L.Np, L.Kp, sh, (int)k12_blocks(m, VL, sh), status, dbg);
+  };
+  // Fewer blocks than CUs: fewer vectors per block, its waves sharing the
+  // planes of the same entries instead.
+  while (sh.vw > 1 && blocks() < 256) sh.vw /= 2;
+  sh.pw = std::min(kK12Waves / (sh.kw * sh.vw), N);
+  if (sh.pw > 1) go(k12_scale_ab<T, false, 2, true>);
+  else go(k12_scale_ab<T, false, 2, false>);
+}
+
 // K3 over the planes given by (t, planes): EPI 0 runs all N planes (t
 // ignored), EPI 1 and 2 one plane.
 template <int EPI>
@@ -358,7 +383,7 @@ void launch_gemm_blocked(int cfg, const int8_t* RA, const int8_t* RB, uint8_t* U
 
 template <int S, typename TO>
 void launch_crt(const Layout& L, char* ws, const ModTable* tab, int N, int64_t m, int64_t n,
-                TO* C, int64_t ldc) {
+                TO* C, int64_t ldc, int* status) {
   const int64_t blocks = ((m + 31) / 32) * ((n + 31) / 32);
   // four waves per 32 x 32 block when two would leave fewer than four
   // waves per SIMD (1024 SIMDs)
@@ -366,12 +391,12 @@ void launch_crt(const Layout& L, char* ws, const ModTable* tab, int N, int64_t m
     const int64_t waves = blocks * kK4WavesPerBlockSmall;
     k4_crt<S, TO, kK4WavesPerBlockSmall><<<(unsigned)((waves + 3) / 4), 256, 0, g_stream>>>(
         (const uint8_t*)(ws + L.U), (const int32_t*)(ws + L.eA), (const int32_t*)(ws + L.eB),
-        tab, N, m, n, L.Mp, L.Np, C, ldc);
+        tab, N, m, n, L.Mp, L.Np, C, ldc, status);
   } else {
     const int64_t waves = blocks * kK4WavesPerBlock;
     k4_crt<S, TO><<<(unsigned)((waves + 3) / 4), 256, 0, g_stream>>>(
         (const uint8_t*)(ws + L.U), (const int32_t*)(ws + L.eA), (const int32_t*)(ws + L.eB),
-        tab, N, m, n, L.Mp, L.Np, C, ldc);
+        tab, N, m, n, L.Mp, L.Np, C, ldc, status);
   }
 }
 
@@ -421,10 +446,15 @@ int run_gemm(int64_t m, int64_t n, int64_t k, const T* A, int64_t lda, const T* 
     return rc;
   }
 
+  // Whole vectors per block: norms, exponents and conversion in one kernel
+  // (stage 1).
+  const bool k12 = !fused && (mode == OZ2_MODE_REVISED || mode == OZ2_MODE_ORIGINAL) &&
+                   HT.limbs == 2 && k <= kK12MaxK;
+
   StageClock clk(!fixed_ws);
   clk.mark(0);
   // K1: squared norms and exponents.
-  {
+  if (!k12) {
     double* pmA = L.maxA ? (double*)(ws + L.maxA) : nullptr;
     double* pmB = L.maxB ? (double*)(ws + L.maxB) : nullptr;
     dim3 gA((unsigned)((m + 63) / 64), (unsigned)((L.nch + 3) / 4));
@@ -526,7 +556,8 @@ int run_gemm(int64_t m, int64_t n, int64_t k, const T* A, int64_t lda, const T* 
     return 0;
   }
   // K2: integers and residues.
-  switch (HT.limbs) {
+  if (k12) launch_k12<T>(A, lda, B, ldb, m, n, k, L, ws, tab, N, mode, dbg != nullptr);
+  else switch (HT.limbs) {
     case 2: launch_split<T, 2>(A, lda, B, ldb, m, n, k, L, ws, tab, N); break;
     case 3: launch_split<T, 3>(A, lda, B, ldb, m, n, k, L, ws, tab, N); break;
     default: launch_split<T, 4>(A, lda, B, ldb, m, n, k, L, ws, tab, N); break;
@@ -571,11 +602,12 @@ int run_gemm(int64_t m, int64_t n, int64_t k, const T* A, int64_t lda, const T* 
   clk.mark(3);
   // K4: CRT and unscaling.
   if (!dbg) {
+    int* st = k12 ? (int*)(ws + L.status) : nullptr;
     switch (HT.slices) {
-      case 1: launch_crt<1, TO>(L, ws, tab, N, m, n, C, ldc); break;
-      case 2: launch_crt<2, TO>(L, ws, tab, N, m, n, C, ldc); break;
-      case 3: launch_crt<3, TO>(L, ws, tab, N, m, n, C, ldc); break;
-      default: launch_crt<4, TO>(L, ws, tab, N, m, n, C, ldc); break;
+      case 1: launch_crt<1, TO>(L, ws, tab, N, m, n, C, ldc, st); break;
+      case 2: launch_crt<2, TO>(L, ws, tab, N, m, n, C, ldc, st); break;
+      case 3: launch_crt<3, TO>(L, ws, tab, N, m, n, C, ldc, st); break;
+      default: launch_crt<4, TO>(L, ws, tab, N, m, n, C, ldc, st); break;
     }
   }
   clk.mark(4);
@@ -842,14 +874,18 @@ int plan_batch(int batch, const oz2_problem* P, int mode, size_t tune_ops, Batch
     for (int a = 0; a < na; ++a) {
       const oz2_problem& q = P[pl->act[a]];
       const Layout& L = pl->lay[a];
+      const bool k12 = q.k <= kK12MaxK;
+      const K12Shape sh = k12_shape<kK12VL<double>>(L.Kp);
       int64_t c = 0;
       switch (st) {
-        case kB_K1A: c = ((q.m + 63) / 64) * ((L.nch + 3) / 4); break;
-        case kB_K1B: c = (q.n * L.nch + 255) / 256; break;
-        case kB_FOLDA: c = (q.m + 255) / 256; break;
-        case kB_FOLDB: c = (q.n + 255) / 256; break;
-        case kB_K2A: c = (L.Mp / kK2VB) * (L.Kp / kK2HB); break;
-        case kB_K2B: c = (L.Np * (L.Kp / kK2EPT) + 255) / 256; break;
+        case kB_K12A: c = k12 ? k12_blocks(q.m, kK12VL<double>, sh) : 0; break;
+        case kB_K12B: c = k12 ? k12_blocks(q.n, kK12VL<double>, sh) : 0; break;
+        case kB_K1A: c = k12 ? 0 : ((q.m + 63) / 64) * ((L.nch + 3) / 4); break;
+        case kB_K1B: c = k12 ? 0 : (q.n * L.nch + 255) / 256; break;
+        case kB_FOLDA: c = k12 ? 0 : (q.m + 255) / 256; break;
+        case kB_FOLDB: c = k12 ? 0 : (q.n + 255) / 256; break;
+        case kB_K2A: c = k12 ? 0 : (L.Mp / kK2VB) * (L.Kp / kK2HB); break;
+        case kB_K2B: c = k12 ? 0 : (L.Np * (L.Kp / kK2EPT) + 255) / 256; break;
         default: c = (((q.m + 31) / 32) * ((q.n + 31) / 32) * kK4WavesPerBlock + 3) / 4; break;
       }
       pl->prefix[(size_t)st * (na + 1) + a] = acc;
@@ -860,7 +896,7 @@ int plan_batch(int batch, const oz2_problem* P, int mode, size_t tune_ops, Batch
     if (acc > INT32_MAX) return OZ2_ERR_TOO_LARGE;
   }
   // the A and B halves of a step share one launch
-  for (int st : {kB_K1A, kB_FOLDA, kB_K2A})
+  for (int st : {kB_K12A, kB_K1A, kB_FOLDA, kB_K2A})
     if (pl->blocks[st] + pl->blocks[st + 1] > INT32_MAX) return OZ2_ERR_TOO_LARGE;
   pl->total_blocks = 0;
   for (int st = 0; st < kB_NSTAGES; ++st) {
@@ -962,6 +998,9 @@ void enqueue_batch(hipStream_t s, const BatchPlan& pl, char* ws, int64_t gemm_gr
   OZ2_STAGE_PAIR(kB_K1A, kB_K1B)
   OZ2_STAGE_PAIR(kB_FOLDA, kB_FOLDB)
   if (clk) clk->mark(1);
+  if (pl.blocks[kB_K12A] > 0)
+    kb_k12<<<(unsigned)(pl.blocks[kB_K12A] + pl.blocks[kB_K12B]), 64 * kK12Waves, 0, s>>>(
+        d_probs, d_prefix, d_owner + pl.owner_off[kB_K12A], na, pl.blocks[kB_K12A], d_status);
   OZ2_STAGE_PAIR(kB_K2A, kB_K2B)
   if (clk) clk->mark(2);
   kb_gemm<<<(unsigned)gemm_grid, 256, 0, s>>>(d_probs, (const WorkItem*)(ws + pl.off_items),
