@@ -1,25 +1,32 @@
-// oz2_fused.hpp -- K2 for A, K3 and K4 in one kernel when n <= 64.
+// oz2_fused.hpp -- K2 for the long operand, K3 and K4 in one kernel when the
+// other operand is narrow: n <= 64 columns of B (the long operand is A, its
+// rows strided) or m <= 64 rows of A (the long operand is B, its columns
+// contiguous; the same product transposed).
 //
-// For a narrow B (n <= 64 columns) the unfused path is bound by memory: K2
-// writes N residue bytes per entry of A, K3 reads them back once (a single
-// tile column), and K4 reads the N product planes.  Here a wave owns 16 rows
-// of C and all n <= 64 columns for every modulus at once (16 x 64 INT32
-// accumulators per plane: 16 registers per lane, 16 planes at most), so it
-//   * reads its rows of A (binary64) once, k step by k step, and forms the
-//     integers and residues in registers (K2's arithmetic, Step 2 and the
-//     residue part of Step 3);
-//   * multiplies them with the residues of B (made by K2 beforehand, staged
-//     through LDS, shared by the four waves of a workgroup) on
-//     v_mfma_i32_16x16x64_i8;
-//   * reduces every product modulo p_t and reconstructs and unscales the
-//     results in registers (K4's arithmetic, Step 3's CRT and Step 4),
-//     writing C directly.
-// No residue plane of A and no product plane is stored.  The results are the
-// unfused path's, bit for bit.
+// For a narrow operand the separate kernels are bound by memory: K2 writes N
+// residue bytes per entry of the long operand, K3 reads them back once (a
+// single row or column of tiles), and K4 reads the N product planes.  Here a
+// workgroup owns 64 vectors of the long operand against all <= 64 of the
+// narrow one and every modulus, 64 x 64 INT32 products per plane spread over
+// the accumulators of 8 waves.  Per step of 64 k it
+//   * converts its 64 x 64 entries (each once, 8 per lane; K2's arithmetic)
+//     and writes the residues of all planes to LDS;
+//   * multiplies them with the narrow operand's residues (made by K2
+//     beforehand, brought to LDS during the conversion) on
+//     v_mfma_i32_32x32x32_i8: wave w takes the 32 x 32 block w % 4 of the
+//     planes of parity w / 4;
+// and at the end reduces the products modulo p_t into LDS bytes, from which
+// each lane reconstructs and unscales 8 outputs (K4's arithmetic).  No residue
+// plane of the long operand and no product plane is stored.  The results are
+// the separate kernels', bit for bit.
 //
-// 16x16x64 INT8 MFMA lane layout (checked on the device): lane l supplies
-// row l % 16 of A and column l % 16 of B with the 16 k bytes of group l / 16;
-// accumulator r of lane l is row 4 (l / 16) + r, column l % 16.
+// Bound: the residues' arithmetic (about 4.75 N + 8 operations per entry).
+// Two waves per SIMD (at most 128 accumulators each) rather than one with all
+// moduli of 16 vectors: alone on its SIMD a wave issues an operation at best
+// every 5.3 cycles, and a dependent binary64 one every 11 (two waves: 5.9).
+// 65536 x 64 x 4096, N = 14: 1.08 ms (1.28 with one wave per SIMD), 2.15 GB
+// read at 2.0 TB/s; the transposed shape 1.09 ms (2.0 ms in the separate
+// kernels).
 #pragma once
 
 #include <utility>
@@ -31,15 +38,22 @@
 
 namespace oz2 {
 
-constexpr int kFuseCols = 64;   // n <= kFuseCols
-constexpr int kFuseMaxN = 16;   // moduli: every plane's accumulators stay in registers
-constexpr int kFuseK = 64;      // k per step (one MFMA)
-constexpr int kFuseRows = 64;   // rows of C per workgroup (4 waves x 16)
+constexpr int kFuseCols = 64;   // vectors of the narrow operand
+constexpr int kFuseMaxN = 16;   // moduli: accumulators and LDS
+constexpr int kFuseK = 64;      // k per step
+constexpr int kFuseRows = 64;   // vectors of the long operand per workgroup
+constexpr int kFuseThreads = 512;
+// Vectors of the long operand from which this kernel is taken: one block of
+// 64 per CU and step of 64 k in about 4.2 us (N = 14), however few the
+// blocks.  64 narrow vectors, k = 4096: 8192 long ones (128 blocks) 305 us
+// for 382 with the separate kernels, but k = 1024: 95 for 72, and 2048 long
+// ones 276 for 193; 16384 x 512: 70 for 74, x 4096: 366 for 698.
+constexpr int kFuseMinLong = 192 * kFuseRows;
 
-// 16-byte chunk position of logical k chunk g in the LDS row of column c
-// (rows of 64 bytes): spreads the 16-byte fragment reads of 8 consecutive
-// columns over distinct banks.
-__device__ __forceinline__ int fuse_swz(int c, int g) { return g ^ ((c >> 1) & 3); }
+// 16-byte chunk position of logical k chunk g in the LDS row of vector c
+// (rows of 64 bytes): spreads the 16-byte fragment reads, and the 8-byte
+// writes of the converted residues, of 16 consecutive vectors over all banks.
+__device__ __forceinline__ int fuse_swz(int c, int g) { return g ^ ((c >> 2) & 3); }
 
 // Number of 39-bit CRT slices for the first NP moduli (P < 2^128 for NP <= 16),
 // as the host tables compute it.
@@ -60,6 +74,33 @@ constexpr double fuse_pow40(int p) {
   return (double)r;
 }
 
+constexpr double kFuseMagic = 0x1.8p52;
+
+// 8 bytes per lane to LDS address a + off.  As asm, since the compiler
+// cannot tell these writes from the direct global->LDS loads in flight to
+// the other array and would wait for them first; the caller waits (lgkmcnt)
+// before the barrier.
+template <int OFF>
+__device__ __forceinline__ void lds_write8(uint32_t a, uint32_t lo, uint32_t hi) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+  const u2 w = {lo, hi};
+  asm volatile("ds_write_b64 %0, %1 offset:%2" ::"v"(a), "v"(w), "n"(OFF) : "memory");
+#endif
+}
+// The value is computed here, not later.
+__device__ __forceinline__ void fuse_pin(double& x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" : "+v"(x));
+#endif
+}
+template <int N>
+__device__ __forceinline__ void wait_vmem_n_lds_all() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
+#endif
+}
+
 template <typename F, int... I>
 __device__ __forceinline__ void fuse_for_impl(F&& f, std::integer_sequence<int, I...>) {
   (f(std::integral_constant<int, I>{}), ...);
@@ -70,187 +111,234 @@ __device__ __forceinline__ void fuse_for(F&& f) {
   fuse_for_impl(f, std::make_integer_sequence<int, NP>{});
 }
 
-// Residue of a' (two limbs) for modulus index t, in the low byte of the
-// result (what the packing reads): as residue_256_byte / residue_odd with
-// the table values of modulus t.
-template <int t>
-__device__ __forceinline__ int fuse_residue(const Limbs<2>& L) {
+// |a'| < 2^51 for the first 13 moduli (P < 2^103): one limb, no fold.
+template <int NP>
+constexpr int kFuseLimbs = NP <= 13 ? 1 : 2;
+
+// Residue of a' for modulus index t, in the low byte of the result (what the
+// packing reads): as residue_256_byte / residue_odd with the table values of
+// modulus t.  One limb: |a'| < 2^51, so the quotient's error |a' / p| 2^-53 <
+// 2^-2 / p stays below the 1 / (2p) distance from a half-integer, and
+// 1.5 2^52 - q p stays in the binade of 1.5 2^52.
+template <int t, int LIMBS>
+__device__ __forceinline__ uint32_t fuse_residue(const Limbs<LIMBS>& L) {
   if constexpr (t == 0) {
-    return (int)residue_256_byte<2>(L);
+    return residue_256_byte<LIMBS>(L);
   } else {
     constexpr double p = (double)kModuli[t], ip = 1.0 / (double)kModuli[t];
-    constexpr double c1 = fuse_pow40(kModuli[t]);
-    const double y = fma(L.x[1], sconst(c1), L.x[0]);
-    const double q = rint(y * ip);
-    return (int)fma(-q, p, y);
+    double y = L.x[0];
+    if constexpr (LIMBS == 2) y = fma(L.x[1], sconst(fuse_pow40(kModuli[t])), y);
+    const double tq = fma(y, sconst(ip), kFuseMagic);
+    const double s = fma(tq, sconst(-p), kFuseMagic * (p + 1.0));
+    return (uint32_t)f64_to_bits(s + y);
   }
 }
 
-// Limbs of trunc(a 2^e) for this kernel, whose residues of A are never
-// stored.  A row with a non-finite entry (exponent sentinel) gets a very
-// negative exponent instead, so that its finite entries truncate to 0, and
-// every value is clamped to [-2^78, 2^78] (infinities; NaNs too, since the
-// minimum and maximum return the operand that is not a NaN): its residues
-// are well-defined integers, and its outputs are NaN whatever its products
-// are.  For every other row |a'| < 2^64 (P < 2^128 for N <= 16), so the clamp
-// changes nothing and the limbs are make_limbs<2>'s.
-__device__ __forceinline__ Limbs<2> fuse_limbs(double a, int32_t e) {
+// Limbs of trunc(a 2^e) for this kernel, whose residues of the long operand
+// are never stored.  A vector with a non-finite entry (exponent sentinel)
+// gets a very negative exponent instead, so that its finite entries truncate
+// to 0, and every value is clamped (infinities; NaNs too, since the minimum
+// and maximum return the operand that is not a NaN): its residues are
+// well-defined integers, and its outputs are NaN whatever its products are.
+// For every other vector |a'| is below the clamp (P < 2^128 for N <= 16).
+template <int LIMBS>
+__device__ __forceinline__ Limbs<LIMBS> fuse_limbs(double a, int32_t e) {
+  constexpr double kClamp = LIMBS == 1 ? 0x1p50 * 1.999 : 0x1p78;
   const double v =
-      __builtin_fmin(__builtin_fmax(trunc(ldexp(a, e)), sconst(-0x1p78)), sconst(0x1p78));
-  Limbs<2> L;
-  L.x[1] = trunc(v * 0x1p-40);
-  L.x[0] = fma(-L.x[1], 0x1p40, v);
+      __builtin_fmin(__builtin_fmax(trunc(ldexp(a, e)), sconst(-kClamp)), sconst(kClamp));
+  Limbs<LIMBS> L;
+  if constexpr (LIMBS == 1) {
+    L.x[0] = v;
+  } else {
+    L.x[1] = trunc(v * 0x1p-40);
+    L.x[0] = fma(-L.x[1], 0x1p40, v);
+  }
   return L;
 }
 
-// NP = N (a template parameter, so that every accumulator access and product
-// is unconditional and the accumulators stay in the accumulation registers).
-template <typename T, typename TO, int NP>
-__global__ __launch_bounds__(256) void k234_fused(
-    const T* __restrict__ A, int64_t lda, int64_t m, int64_t n, int64_t k,
-    const int32_t* __restrict__ eA, const int32_t* __restrict__ eB,
-    const int8_t* __restrict__ RB, int64_t Np, int64_t Kp,
-    const ModTable* __restrict__ tab, TO* __restrict__ C, int64_t ldc) {
+// X: the long operand, entry h of vector v at X[v + h ld] or (CONTIG)
+// X[v ld + h]; nx vectors, exponents eX.  RW: the narrow operand's residue
+// planes (kFuseCols rows of Kp bytes each), nw vectors, exponents eW.  Output
+// (x, w) at C[x + w ldc] or (CONTIG) C[w + x ldc].  NP = N, a template
+// parameter: the moduli and their constants are compile-time values, and
+// every accumulator access is unconditional.
+template <typename T, typename TO, int NP, bool CONTIG>
+__global__ __launch_bounds__(kFuseThreads, 2) void k234_fused(
+    const T* __restrict__ X, int64_t ld, int64_t nx, int64_t nw, int64_t k,
+    const int32_t* __restrict__ eX, const int32_t* __restrict__ eW,
+    const int8_t* __restrict__ RW, int64_t Kp, const ModTable* __restrict__ tab,
+    TO* __restrict__ C, int64_t ldc) {
   static_assert(NP >= 2 && NP <= kFuseMaxN, "moduli");
-  constexpr int S = fuse_slices(NP);
-  constexpr int N = NP;
-  constexpr int PB = kFuseCols * kFuseK;   // bytes of B residues per plane and step
-  __shared__ __attribute__((aligned(16))) int8_t lds[2][NP * PB];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t row0 = (int64_t)blockIdx.x * kFuseRows + wave * 16;
-  const int64_t arow = row0 + (lane & 15);           // the row of A this lane converts
-  const bool rowok = arow < m;
-  // rows beyond m convert to zero through the non-finite sentinel (their
+  constexpr int S = fuse_slices(NP), LIMBS = kFuseLimbs<NP>;
+  constexpr int HP = (NP + 1) / 2;                   // planes per wave
+  constexpr int PB = 64 * kFuseK;                    // bytes per plane and step
+  __shared__ __attribute__((aligned(16))) int8_t ldsX[NP * PB];
+  __shared__ __attribute__((aligned(16))) int8_t ldsW[NP * PB];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t x0 = (int64_t)blockIdx.x * kFuseRows;
+
+  // Conversion: this lane's vector xl and its 8 entries from kc of a step (a
+  // wave reads 64 entries of a column of a strided operand, or 8 rows of 64
+  // entries of a contiguous one).
+  const int xl = CONTIG ? wave * 8 + (lane >> 3) : lane;
+  const int kc = CONTIG ? (lane & 7) * 8 : wave * 8;
+  const int64_t xv = x0 + xl;
+  const bool xok = xv < nx;
+  // vectors beyond nx convert to zero through the non-finite sentinel (their
   // outputs are never written)
-  const int32_t ea0 = rowok ? eA[arow] : kExpNonFinite;
-  const int32_t ea = ea0 == kExpNonFinite ? -2000 : ea0;   // see fuse_limbs
-  const T* Ap = A + (rowok ? arow : 0);               // clamped: every load in bounds
-  const int kq = (lane >> 4) * 16;                    // this lane's k bytes in a step
-
-  // B slab of a step: lane tid fills LDS slot tid of every plane, column
-  // tid / 4, stored chunk tid % 4 (holding logical chunk fuse_swz(col, tid % 4),
-  // the swizzle being an involution).
-  const int bcol = tid >> 2;
-  const int64_t boff = (int64_t)bcol * Kp + fuse_swz(bcol, tid & 3) * 16;
-  auto load_b = [&](int buf, int64_t k0) {
+  const int32_t e0 = xok ? eX[xv] : kExpNonFinite;
+  const int32_t ex = e0 == kExpNonFinite ? -2000 : e0;   // see fuse_limbs
+  const T* Xp = X + (xok ? xv : nx - 1) * (CONTIG ? ld : 1);
+  const int64_t st = CONTIG ? 1 : ld;
+  typedef __attribute__((address_space(3))) int8_t LdsByte;
+  const uint32_t xdst = (uint32_t)(uintptr_t)(LdsByte*)(ldsX + xl * kFuseK +
+                                                        fuse_swz(xl, kc >> 4) * 16 + (kc & 8));
+  // The fewest load instructions load_x can take (16 bytes each at most): so
+  // many may still be in flight when the narrow operand's slab is needed.
+  constexpr int kXLoads = CONTIG ? 8 * (int)sizeof(T) / 16 : 8;
+  double raw[8];
+  // Only the last steps can run past k: there out-of-range k reads the last
+  // entry (in bounds) and the value is zeroed when used.
+  auto load_x = [&](int64_t k0) {
+    const int64_t kb = k0 + kc;
+    if (k0 + kFuseK <= k) {
+      const T* p = Xp + kb * st;
+      if constexpr (CONTIG) {
+        constexpr int V = 16 / sizeof(T);
+        typedef T Piece __attribute__((ext_vector_type(V), aligned(sizeof(T))));
 #pragma unroll
-    for (int t = 0; t < NP; ++t)
-      load_lds16(RB + (int64_t)t * Np * Kp + boff + k0, lds[buf] + t * PB + wave * 64 * 16);
-  };
-  // A values of a step: 16 consecutive k of one row, lda apart.  Only the
-  // last step can run past k: there out-of-range k reads the last column
-  // (in bounds) and the value is zeroed when used.
-  auto load_a = [&](int64_t k0, double (&raw)[16]) {
-    const int64_t kb = k0 + kq;
-    if (kb + 16 <= k) {
-      const T* p = Ap + kb * lda;
+        for (int i = 0; i < 8 / V; ++i) {
+          const Piece q = *reinterpret_cast<const Piece*>(p + i * V);
 #pragma unroll
-      for (int j = 0; j < 16; ++j) raw[j] = (double)__builtin_nontemporal_load(p + j * lda);
-    } else {
+          for (int j = 0; j < V; ++j) raw[i * V + j] = (double)q[j];
+        }
+      } else {
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const int64_t kk = kb + j;
-        const int64_t kc = kk < k ? kk : k - 1;
-        raw[j] = (double)__builtin_nontemporal_load(Ap + kc * lda);
+        for (int j = 0; j < 8; ++j) raw[j] = load_in<true>(p + j * st);
       }
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) raw[j] = (double)Xp[(kb + j < k ? kb + j : k - 1) * st];
     }
   };
-
-  v4i acc[NP][4];
+  // Narrow operand, half of the planes per 256 lanes: lane fills LDS slot
+  // tid % 256 of a plane (vector / 4, stored chunk % 4, the swizzle being an
+  // involution).
+  const int wrow = (tid & 255) >> 2, whalf = (wave >> 2) & 1;
+  const int64_t woff = (int64_t)wrow * Kp + fuse_swz(wrow, tid & 3) * 16;
+  auto load_w = [&](int64_t k0) {
 #pragma unroll
-  for (int t = 0; t < NP; ++t)
-#pragma unroll
-    for (int cb = 0; cb < 4; ++cb) acc[t][cb] = v4i{0, 0, 0, 0};
+    for (int t = 0; t < HP; ++t)
+      if (2 * t + whalf < NP)
+        load_lds16(RW + (int64_t)(2 * t + whalf) * kFuseCols * Kp + woff + k0,
+                   ldsW + (2 * t + whalf) * PB + (wave & 3) * 64 * 16);
+  };
 
-  const int nsteps = (int)(Kp / kFuseK);
-  double raw[16];
-  load_b(0, 0);
-  load_a(0, raw);
+  const int bx = (wave >> 1) & 1, bw = wave & 1, half = (wave >> 2) & 1;
+  v16i acc[HP];
+#pragma unroll
+  for (int t = 0; t < HP; ++t) acc[t] = v16i{0};
+
+  const int nsteps = (int)((k + kFuseK - 1) / kFuseK);
+  load_x(0);
   for (int s = 0; s < nsteps; ++s) {
-    const int buf = s & 1;
     const int64_t k0 = (int64_t)s * kFuseK;
-    if (k0 + kq + 16 > k) {
+    if (k0 + kc + 8 > k) {
 #pragma unroll
-      for (int j = 0; j < 16; ++j)
-        if (k0 + kq + j >= k) raw[j] = 0.0;
+      for (int j = 0; j < 8; ++j)
+        if (k0 + kc + j >= k) raw[j] = 0.0;
     }
-    Limbs<2> L[16];
+    Limbs<LIMBS> L[8];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) L[j] = fuse_limbs(raw[j], ea);
-    const bool more = s + 1 < nsteps;
-    if (more) {
-      load_a(k0 + kFuseK, raw);
-      wait_vmem_n<16>();   // all but the 16 A loads just issued: slab s is in LDS
-    } else {
-      wait_vmem_all();
-    }
-    __syncthreads();       // every wave's part of slab s; every wave done with slab s - 1
-    if (more) load_b(buf ^ 1, k0 + kFuseK);
-    // One plane at a time (fences keep the scheduler from hoisting every
-    // plane's work, which would exhaust the registers): the plane's four
-    // fragment reads first, so that its residue arithmetic covers their
-    // latency, then the products.
+    for (int j = 0; j < 8; ++j) L[j] = fuse_limbs<LIMBS>(raw[j], ex);
+    // the entries are in, and used, before more loads go out (a wait for them
+    // behind those would wait for those too)
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+#pragma unroll
+      for (int i = 0; i < LIMBS; ++i) fuse_pin(L[j].x[i]);
+    __builtin_amdgcn_sched_barrier(0);
+    load_w(k0);                          // lands during the conversion
+    if (s + 1 < nsteps) load_x(k0 + kFuseK);
     fuse_for<NP>([&](auto tc) {
       constexpr int t = decltype(tc)::value;
-      v4i bf[4];
-#pragma unroll
-      for (int cb = 0; cb < 4; ++cb) {
-        const int col = cb * 16 + (lane & 15);
-        bf[cb] = *reinterpret_cast<const v4i*>(lds[buf] + t * PB + col * kFuseK +
-                                               fuse_swz(col, lane >> 4) * 16);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      uint32_t w[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        w[q] = pack_low_bytes(fuse_residue<t>(L[4 * q]), fuse_residue<t>(L[4 * q + 1]),
-                              fuse_residue<t>(L[4 * q + 2]), fuse_residue<t>(L[4 * q + 3]));
-      const v4i af = {(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int cb = 0; cb < 4; ++cb)
-        acc[t][cb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(af, bf[cb], acc[t][cb], 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
+      lds_write8<t * PB>(xdst,
+                         pack_low_bytes(fuse_residue<t>(L[0]), fuse_residue<t>(L[1]),
+                                        fuse_residue<t>(L[2]), fuse_residue<t>(L[3])),
+                         pack_low_bytes(fuse_residue<t>(L[4]), fuse_residue<t>(L[5]),
+                                        fuse_residue<t>(L[6]), fuse_residue<t>(L[7])));
+      __builtin_amdgcn_sched_barrier(0);   // one plane at a time (registers)
     });
+    // the narrow operand's slab of this step has landed (the next entries of
+    // the long one may still be on their way)
+    if (s + 1 < nsteps) wait_vmem_n_lds_all<kXLoads>();
+    else wait_vmem_lds_all();
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < HP; ++t) {
+      if (2 * t + half < NP) {
+        const int8_t* px = ldsX + (2 * t + half) * PB;
+        const int8_t* pw = ldsW + (2 * t + half) * PB;
+        const int rx = bx * 32 + (lane & 31), rw = bw * 32 + (lane & 31);
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+          const int g = kk * 2 + (lane >> 5);
+          const v4i fx = *reinterpret_cast<const v4i*>(px + rx * kFuseK + fuse_swz(rx, g) * 16);
+          const v4i fw = *reinterpret_cast<const v4i*>(pw + rw * kFuseK + fuse_swz(rw, g) * 16);
+          acc[t] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fx, fw, acc[t], 0, 0, 0);
+        }
+      }
+    }
+    __syncthreads();       // every wave is done with this step's slabs
   }
 
-  // Epilogue: per output, U_t = C_t mod p_t in [0, p_t) (as the GEMM's own
-  // epilogue computes it), the exact CRT sum, reconstruction and unscaling
-  // (as K4 does).
+  // Epilogue: the residues of the products as bytes in LDS, plane by plane
+  // [vector along the contiguous side of C][other vector], in ldsX.
+#pragma unroll
+  for (int t = 0; t < HP; ++t) {
+    if (2 * t + half < NP) {
+      const int tt = 2 * t + half;
+      const double p = tab->p[tt], ip = tt == 0 ? 0.0 : tab->inv_p[tt];  // 256: the low byte
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int rx = bx * 32 + acc_row(r, lane), rw = bw * 32 + acc_col(lane);
+        ldsX[tt * PB + (CONTIG ? rw * 64 + rx : rx * 64 + rw)] =
+            (int8_t)residue_sym_i32(acc[t][r], p, ip);
+      }
+    }
+  }
+  __syncthreads();
+  // Lane = the vector along C's columns; outputs 8 wave .. 8 wave + 7 across.
+  double sums[8][S];
+#pragma unroll
+  for (int j = 0; j < 8; ++j)
+#pragma unroll
+    for (int q = 0; q < S; ++q) sums[j][q] = 0.0;
+  for (int t = 0; t < NP; ++t) {
+    const uint2 b = *reinterpret_cast<const uint2*>(ldsX + t * PB + lane * 64 + wave * 8);
+    double wt[S];
+#pragma unroll
+    for (int q = 0; q < S; ++q) wt[q] = tab->w[t][q];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const double u = (double)(int)(int8_t)((j < 4 ? b.x : b.y) >> (8 * (j & 3)));
+#pragma unroll
+      for (int q = 0; q < S; ++q) sums[j][q] = fma(wt[q], u, sums[j][q]);
+    }
+  }
   const ModTable& TB = *tab;
 #pragma unroll
-  for (int cb = 0; cb < 4; ++cb) {
-    const int64_t col = cb * 16 + (lane & 15);
-    const int32_t f = col < n ? eB[col] : 0;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int64_t row = row0 + 4 * (lane >> 4) + r;
-      double X[S];
-#pragma unroll
-      for (int q = 0; q < S; ++q) X[q] = 0.0;
-#pragma unroll
-      for (int t = 0; t < NP; ++t) {
-        const int c = acc[t][cb][r];
-        double u;
-        if (t == 0) {
-          u = (double)((uint32_t)c & 0xFFu);
-        } else {
-          const double y = (double)c;
-          const double rr = fma(-rint(y * TB.inv_p[t]), TB.p[t], y);  // exact
-          u = rr < 0.0 ? rr + TB.p[t] : rr;
-        }
-#pragma unroll
-        for (int q = 0; q < S; ++q) X[q] = fma(TB.w[t][q], u, X[q]);
-      }
-      if (row < m && col < n) {
-        const int32_t e = eA[row];
-        double v;
-        if (e == kExpNonFinite || f == kExpNonFinite) v = __builtin_nan("");
-        else if constexpr (sizeof(TO) == 8) v = crt_unscale<S, 53, -1074>(X, TB, e + f);
-        else v = crt_unscale<S, 24, -149>(X, TB, e + f);
-        C[row + col * ldc] = (TO)v;
-      }
-      __builtin_amdgcn_sched_barrier(0);
+  for (int j = 0; j < 8; ++j) {
+    const int xi = CONTIG ? wave * 8 + j : lane, wi = CONTIG ? lane : wave * 8 + j;
+    const int64_t x = x0 + xi;
+    if (x < nx && wi < nw) {
+      const int32_t e = eX[x], f = eW[wi];
+      double v;
+      if (e == kExpNonFinite || f == kExpNonFinite) v = __builtin_nan("");
+      else if constexpr (sizeof(TO) == 8) v = crt_unscale<S, 53, -1074>(sums[j], TB, e + f);
+      else v = crt_unscale<S, 24, -149>(sums[j], TB, e + f);
+      C[CONTIG ? wi + x * ldc : x + wi * ldc] = (TO)v;
     }
   }
 }

@@ -127,7 +127,7 @@ int tile_config(int64_t m, int64_t n, int64_t k, int N) {
 // modulus and operand, three uint8 product planes per modulus; the squared
 // norms run over 2k components).
 Layout make_layout(int64_t m, int64_t n, int64_t k, int N, int mode, int64_t bm = kBM,
-                   int64_t bn = kBN, int comps = 1, bool fused = false) {
+                   int64_t bn = kBN, int comps = 1, bool fused_n = false, bool fused_m = false) {
   const bool fp8 = (mode & OZ2_ENGINE_FP8) != 0;
   mode &= ~OZ2_ENGINE_FP8;
   Layout L;
@@ -154,10 +154,11 @@ Layout make_layout(int64_t m, int64_t n, int64_t k, int N, int mode, int64_t bm 
   L.cmaxB = acc ? take(4 * (size_t)L.Np) : 0;
   L.barA = acc ? take((size_t)L.Mp * L.Kp) : 0;
   L.barB = acc ? take((size_t)L.Np * L.Kp) : 0;
-  // the fused path (n <= 64) keeps A's residues and the products in registers
-  L.RA = take(fused ? 0 : (size_t)comps * N * L.Mp * L.Kp);
-  L.RB = take((size_t)comps * N * L.Np * L.Kp);
-  L.U = take(fused ? 0 : (size_t)comps * N * L.Mp * L.Np);
+  // the fused path (n <= 64, or m <= 64) stores only the narrow operand's
+  // residues, and no products
+  L.RA = take(fused_n ? 0 : (size_t)comps * N * L.Mp * L.Kp);
+  L.RB = take(fused_m ? 0 : (size_t)comps * N * L.Np * L.Kp);
+  L.U = take(fused_n || fused_m ? 0 : (size_t)comps * N * L.Mp * L.Np);
   L.FA = fp8 ? take((size_t)N * L.Mp * 2 * L.Kp) : 0;
   L.FB = fp8 ? take((size_t)N * L.Np * 2 * L.Kp) : 0;
   L.total = off;
@@ -243,6 +244,13 @@ int get_workspace(int dev, size_t bytes, char** out, bool keeps_batch_tables = f
   }
   *out = reinterpret_cast<char*>(D.ws);
   return 0;
+}
+
+// Whether get_workspace (or the fixed array of ozaki2_dgemm_noalloc) can
+// supply so many bytes.
+bool workspace_fits(size_t bytes, bool fixed_ws) {
+  if (fixed_ws) return bytes <= (size_t)OZ2_NOALLOC_SCRATCH_BYTES;
+  return g_ws_policy == OZ2_WORKSPACE_LIBRARY || (g_user_ws && g_user_ws_bytes >= bytes);
 }
 
 // Stage timing: each timed call records OZ2_NUM_STAGES + 1 events on the
@@ -430,14 +438,19 @@ int run_gemm(int64_t m, int64_t n, int64_t k, const T* A, int64_t lda, const T* 
   const ModTable* tab = D.d_tables + acc_tab * (kMaxN + 1) + N;
 
   const int cfg = tile_config(m, n, k, N);
-  // Narrow B: conversion of A, products and CRT in one kernel (automatic
-  // tile choice only; a forced tile keeps the separate kernels).
-  const bool fused = !dbg && !fp8 && g_tile_policy == OZ2_TILE_AUTO && n <= kFuseCols &&
-                     N <= kFuseMaxN && mode != OZ2_MODE_ACCURATE && k <= OZ2_K_BLOCK &&
-                     HT.limbs == 2;
-  Layout L = fused ? make_layout(m, n, k, N, mode, kFuseRows, kFuseCols, 1, true)
-             : fp8 ? make_layout(m, n, k, N, mode | OZ2_ENGINE_FP8, kF8Tile, kF8Tile)
-                   : make_layout(m, n, k, N, mode, kTileBM[cfg], kTileBN[cfg]);
+  Layout L = fp8 ? make_layout(m, n, k, N, mode | OZ2_ENGINE_FP8, kF8Tile, kF8Tile)
+                 : make_layout(m, n, k, N, mode, kTileBM[cfg], kTileBN[cfg]);
+  // Narrow B or narrow A: conversion of the other operand, products and CRT
+  // in one kernel (automatic tile choice only; a forced tile keeps the
+  // separate kernels) where its blocks fill most of the chip, or where the
+  // workspace holds only what that kernel needs (narrow B).
+  const bool can_fuse = !dbg && !fp8 && g_tile_policy == OZ2_TILE_AUTO && N <= kFuseMaxN &&
+                        mode != OZ2_MODE_ACCURATE && k <= OZ2_K_BLOCK && HT.limbs == 2;
+  const bool fits = workspace_fits(L.total, fixed_ws);
+  const bool fused_n = can_fuse && n <= kFuseCols && (m >= kFuseMinLong || !fits);
+  const bool fused_m = can_fuse && !fused_n && m <= kFuseCols && n >= kFuseMinLong && fits;
+  const bool fused = fused_n || fused_m;
+  if (fused) L = make_layout(m, n, k, N, mode, kFuseRows, kFuseCols, 1, fused_n, fused_m);
   char* ws = nullptr;
   if (fixed_ws) {
     if (L.total > (size_t)OZ2_NOALLOC_SCRATCH_BYTES) return OZ2_ERR_SCRATCH_TOO_SMALL;
@@ -526,21 +539,30 @@ int run_gemm(int64_t m, int64_t n, int64_t k, const T* A, int64_t lda, const T* 
   }
   clk.mark(1);
   if (fused) {
-    // K2 for B only, then the fused kernel (stage 2: conversion of A,
-    // products, CRT and unscaling).
-    const int64_t work = L.Np * (L.Kp / kK2EPT);
-    k2_split_contig<T, 2><<<(unsigned)((work + 255) / 256), 256, 0, g_stream>>>(
-        B, ldb, n, k, (const int32_t*)(ws + L.eB), tab, N, (int8_t*)(ws + L.RB), L.Np, L.Kp);
-    clk.mark(2);
-    const unsigned grid = (unsigned)((m + kFuseRows - 1) / kFuseRows);
+    // K2 for the narrow operand only, then the fused kernel (stage 2:
+    // conversion of the long one, products, CRT and unscaling).
     const int32_t* eA = (const int32_t*)(ws + L.eA);
     const int32_t* eB = (const int32_t*)(ws + L.eB);
-    const int8_t* RB = (const int8_t*)(ws + L.RB);
+    int8_t* RW = (int8_t*)(ws + (fused_n ? L.RB : L.RA));
+    if (fused_n) {
+      const int64_t work = L.Np * (L.Kp / kK2EPT);
+      k2_split_contig<T, 2><<<(unsigned)((work + 255) / 256), 256, 0, g_stream>>>(
+          B, ldb, n, k, eB, tab, N, RW, L.Np, L.Kp);
+    } else {
+      k2_split_strided<T, 2><<<dim3((unsigned)(L.Mp / kK2VB), (unsigned)(L.Kp / kK2HB)), 256, 0,
+                               g_stream>>>(A, lda, m, k, eA, tab, N, RW, L.Mp, L.Kp);
+    }
+    clk.mark(2);
+    const unsigned grid = (unsigned)(((fused_n ? m : n) + kFuseRows - 1) / kFuseRows);
     switch (N) {
-#define OZ2_FUSED(NP)                                                                     \
-  case NP:                                                                                \
-    k234_fused<T, TO, NP><<<grid, 256, 0, g_stream>>>(A, lda, m, n, k, eA, eB, RB, L.Np,  \
-                                                       L.Kp, tab, C, ldc);                \
+#define OZ2_FUSED(NP)                                                                        \
+  case NP:                                                                                   \
+    if (fused_n)                                                                             \
+      k234_fused<T, TO, NP, false><<<grid, kFuseThreads, 0, g_stream>>>(                     \
+          A, lda, m, n, k, eA, eB, RW, L.Kp, tab, C, ldc);                                   \
+    else                                                                                     \
+      k234_fused<T, TO, NP, true><<<grid, kFuseThreads, 0, g_stream>>>(                      \
+          B, ldb, n, m, k, eB, eA, RW, L.Kp, tab, C, ldc);                                   \
     break;
       OZ2_FUSED(2) OZ2_FUSED(3) OZ2_FUSED(4) OZ2_FUSED(5) OZ2_FUSED(6) OZ2_FUSED(7)
       OZ2_FUSED(8) OZ2_FUSED(9) OZ2_FUSED(10) OZ2_FUSED(11) OZ2_FUSED(12) OZ2_FUSED(13)
