@@ -225,24 +225,35 @@ __global__ __launch_bounds__(256) void k2_split_contig_cplx(
 // rmod(C, p_t) as a signed byte in the GEMM's 32 x 32 block order.  For each
 // entry and modulus re = U0 - U1 and im = U2 - U0 - U1, congruent to the two
 // parts modulo p_t and below 2^9 in magnitude, so the slice sums stay below
-// 2^53 (exact) as in the real case.  One wave per
-// 32 x 32 block; the lane's 16 accumulator-order entries in PASSES passes
-// (two accumulator sets, re and im).  Each entry is stored as one (re, im)
-// pair.
+// 2^53 (exact) as in the real case.  PASSES waves per 32 x 32 block, wave h
+// with the R = 16 / PASSES accumulator-order entries R h .. R h + R - 1 of each
+// lane (two accumulator sets, re and im); the next plane's bytes are loaded
+// before the current one is accumulated.  The results go through a per-wave
+// LDS tile, so that a store instruction writes column segments of 2 R (re,
+// im) pairs.  (4096 x 4096, N = 14: 376 us with one wave per block storing
+// each lane's pairs straight to 32 columns.)
+template <int S>
+constexpr int kK4CPasses = S >= 4 ? 4 : 2;
+
 template <int S, typename TO>
 __global__ __launch_bounds__(256) void k4_crt_cplx(
     const uint8_t* __restrict__ U, const int32_t* __restrict__ eA,
     const int32_t* __restrict__ eB, const ModTable* __restrict__ tab, int N,
-    int64_t m, int64_t n, int64_t Mp, int64_t Np, TO* __restrict__ C, int64_t ldc) {
+    int64_t m, int64_t n, int64_t Mp, int64_t Np, TO* __restrict__ C, int64_t ldc,
+    int* __restrict__ status) {
   using T2 = typename Cplx<TO>::type;
+  constexpr int PASSES = kK4CPasses<S>, R = 16 / PASSES, RW = R / 4, RPW = 2 * R;
+  __shared__ T2 tile[4][RPW][33];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t Mb = Mp / 32, Nb = Np / 32;
-  const int64_t blk = (int64_t)blockIdx.x * 4 + wave;
+  const int64_t wid = (int64_t)blockIdx.x * 4 + wave;
+  const int64_t blk = wid / PASSES;
+  const int h = (int)(wid % PASSES);
   const int64_t mb_used = (m + 31) / 32;
   const int64_t nb_used = (n + 31) / 32;
-  if (blk >= mb_used * nb_used) return;
+  if (blk >= mb_used * nb_used) return;     // whole wave: the tile is per wave
   const int64_t bi = blk % mb_used, bj = blk / mb_used;
-  const uint8_t* src = U + (bj * Mb + bi) * 1024 + lane * 16;
+  const uint8_t* src = U + (bj * Mb + bi) * 1024 + lane * 16 + R * h;
   const int64_t plane = Nb * Mb * 1024;
   const int64_t comp = (int64_t)N * plane;
   const int lc = acc_col(lane);
@@ -250,71 +261,90 @@ __global__ __launch_bounds__(256) void k4_crt_cplx(
   const int32_t f = col < n ? eB[col] : 0;
   const ModTable& T = *tab;
   T2* C2 = reinterpret_cast<T2*>(C);
-  constexpr int PASSES = S >= 4 ? 4 : 2, R = 16 / PASSES;
+  double ar[R][S], ai[R][S];
 #pragma unroll
-  for (int h = 0; h < PASSES; ++h) {
-    double ar[R][S], ai[R][S];
+  for (int r = 0; r < R; ++r)
 #pragma unroll
-    for (int r = 0; r < R; ++r)
+    for (int s = 0; s < S; ++s) ar[r][s] = ai[r][s] = 0.0;
+  auto load_plane = [&](int t, uint32_t (&w)[3][RW]) {
 #pragma unroll
-      for (int s = 0; s < S; ++s) ar[r][s] = ai[r][s] = 0.0;
-    for (int t = 0; t < N; ++t) {
-      uint32_t w[3][R / 4];
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        const uint8_t* q = src + c * comp + (int64_t)t * plane + R * h;
-        if constexpr (R == 8) {
-          const uint2 x = *reinterpret_cast<const uint2*>(q);
-          w[c][0] = x.x;
-          w[c][1] = x.y;
-        } else {
-          w[c][0] = *reinterpret_cast<const uint32_t*>(q);
-        }
-      }
-      double wt[S];
-#pragma unroll
-      for (int s = 0; s < S; ++s) wt[s] = T.w[t][s];
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int sh = 8 * (r & 3);
-        const int u0 = (int)(int8_t)(w[0][r >> 2] >> sh);
-        const int u1 = (int)(int8_t)(w[1][r >> 2] >> sh);
-        const int u2 = (int)(int8_t)(w[2][r >> 2] >> sh);
-        const int re = u0 - u1;
-        const int im = u2 - u0 - u1;
-#pragma unroll
-        for (int s = 0; s < S; ++s) {
-          ar[r][s] = fma(wt[s], (double)re, ar[r][s]);
-          ai[r][s] = fma(wt[s], (double)im, ai[r][s]);
-        }
+    for (int c = 0; c < 3; ++c) {
+      const uint8_t* q = src + c * comp + (int64_t)t * plane;
+      if constexpr (RW == 2) {
+        const uint2 x = *reinterpret_cast<const uint2*>(q);
+        w[c][0] = x.x;
+        w[c][1] = x.y;
+      } else {
+        w[c][0] = *reinterpret_cast<const uint32_t*>(q);
       }
     }
+  };
+  uint32_t w[3][RW], nx[3][RW];
+  load_plane(0, w);
+  for (int t = 0; t < N; ++t) {
+    load_plane(t + 1 < N ? t + 1 : t, nx);
+    double wt[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) wt[s] = T.w[t][s];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const int64_t row = bi * 32 + acc_row(R * h + r, lane);
-      if (row < m && col < n) {
-        const int32_t e = eA[row];
-        T2 out;
-        if (e == kExpNonFinite || f == kExpNonFinite) {
-          out.x = out.y = (TO)__builtin_nan("");
-        } else {
-          double a[S], b[S];
+      const int sh = 8 * (r & 3);
+      const int u0 = (int)(int8_t)(w[0][r >> 2] >> sh);
+      const int u1 = (int)(int8_t)(w[1][r >> 2] >> sh);
+      const int u2 = (int)(int8_t)(w[2][r >> 2] >> sh);
+      const double re = (double)(u0 - u1), im = (double)(u2 - u0 - u1);
 #pragma unroll
-          for (int s = 0; s < S; ++s) {
-            a[s] = ar[r][s];
-            b[s] = ai[r][s];
-          }
-          if constexpr (sizeof(TO) == 8) {
-            out.x = crt_unscale<S, 53, -1074>(a, T, e + f);
-            out.y = crt_unscale<S, 53, -1074>(b, T, e + f);
-          } else {
-            out.x = (TO)crt_unscale<S, 24, -149>(a, T, e + f);
-            out.y = (TO)crt_unscale<S, 24, -149>(b, T, e + f);
-          }
-        }
-        C2[row + col * ldc] = out;
+      for (int s = 0; s < S; ++s) {
+        ar[r][s] = fma(wt[s], re, ar[r][s]);
+        ai[r][s] = fma(wt[s], im, ai[r][s]);
       }
     }
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+      for (int q = 0; q < RW; ++q) w[c][q] = nx[c][q];
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int lr = acc_row(R * h + r, lane);   // RPW h .. RPW h + RPW - 1
+    const int64_t row = bi * 32 + lr;
+    T2 out;
+    out.x = out.y = (TO)0;
+    if (row < m && col < n) {
+      const int32_t e = eA[row];
+      if (e == kExpNonFinite || f == kExpNonFinite) {
+        out.x = out.y = (TO)__builtin_nan("");
+        if (status) atomicOr(status, 1);       // where no earlier kernel could set it
+      } else {
+        double a[S], b[S];
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+          a[s] = ar[r][s];
+          b[s] = ai[r][s];
+        }
+        if constexpr (sizeof(TO) == 8) {
+          out.x = crt_unscale<S, 53, -1074>(a, T, e + f);
+          out.y = crt_unscale<S, 53, -1074>(b, T, e + f);
+        } else {
+          out.x = (TO)crt_unscale<S, 24, -149>(a, T, e + f);
+          out.y = (TO)crt_unscale<S, 24, -149>(b, T, e + f);
+        }
+      }
+    }
+    tile[wave][lr - RPW * h][lc] = out;
+  }
+  // LDS operations of one wave complete in order; the fence keeps the
+  // compiler from moving the reads above the writes.
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  const int orow = lane % RPW;
+  const int64_t row = bi * 32 + RPW * h + orow;
+#pragma unroll
+  for (int i = 0; i < RPW / 2; ++i) {
+    const int oc = (64 / RPW) * i + lane / RPW;
+    const int64_t c = bj * 32 + oc;
+    if (row < m && c < n) C2[row + c * ldc] = tile[wave][orow][oc];
   }
 }
 

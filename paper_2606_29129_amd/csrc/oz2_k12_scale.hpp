@@ -23,7 +23,9 @@
 // written; 120 us with the stores left out, 3.5 TB/s against 4.6 TB/s for a
 // plain copy) where the three kernels took 236 us; small calls are latency:
 // 256^3 7.3 us for 16.8, 1024^3 16.1 for 25.1; batch of 256 problems (sides
-// 64..2048) 1.20 ms for 1.55.
+// 64..2048) 1.20 ms for 1.55.  Complex 4096 x 4096 operands, N = 14: 660 us
+// (one block per CU: its three components do not fit the registers of two)
+// for 706 in seven launches.
 #pragma once
 
 #include "oz2_k1_norm.hpp"
@@ -42,17 +44,20 @@ constexpr int kK12Waves = 8;   // waves per block
 // column per load instruction.
 template <typename T>
 constexpr int kK12VL = sizeof(T) == 8 ? 8 : 16;
+// Complex vectors (real vectors of 2k components in storage order; 8 entries
+// per lane, 128 per wave and vector): whole 128-byte segments of the planes.
+constexpr int kK12VLCplx = 4;
 
 // How a block's waves are dealt out: kw along k, vw to further vectors, pw to
 // parts of the planes (wave groups that convert the same entries for every
-// pw-th modulus; 1 unless SPLIT).  A block owns VB = vw VL vectors, a power of two and at
-// most 64, so that every block stays inside the padded vectors.
+// pw-th modulus; 1 unless SPLIT).  A block owns VB = vw VL vectors, a power
+// of two and at most 64, so that every block stays inside the padded vectors.
 struct K12Shape {
   int kw, vw, pw;
 };
 template <int VL>
-OZ2_HD K12Shape k12_shape(int64_t Kp) {
-  const int nkb = (int)(Kp / (1024 / VL));
+OZ2_HD K12Shape k12_shape(int64_t K) {   // K: padded components of a vector
+  const int nkb = (int)(K / (1024 / VL));
   const int kw = nkb < kK12Waves ? nkb : kK12Waves, q = kK12Waves / kw;
   int vw = 1;
   while (2 * vw <= q && 2 * vw * VL <= 64) vw *= 2;
@@ -65,20 +70,73 @@ inline int64_t k12_blocks(int64_t nvec, int VL, const K12Shape& sh) {
   return (nvec + sh.vw * VL - 1) / (sh.vw * VL);
 }
 
-// Doubles of LDS for the chunk sums: VB ceil(k / 64) at most.
-template <int VL>
-constexpr int kK12Part = (VL * kK12MaxK / kKC) > 256 ? (VL * kK12MaxK / kKC) : 256;
+// Doubles of LDS for the chunk sums: VB ceil(K / 64) at most, for K <= MAXK
+// components.
+template <int VL, int MAXK>
+constexpr int kK12Part = (VL * MAXK / kKC) > 256 ? (VL * MAXK / kKC) : 256;
+
+// Residue modulo an odd p of a limb sum y (residue_odd's last three steps).
+OZ2_HD uint32_t residue_of_sum(double y, double p, double ip) {
+  constexpr double kMagic = 0x1.8p52;
+  const double tq = fma(y, ip, kMagic);
+  const double s = fma(tq, -p, kMagic * (p + 1.0));
+  return (uint32_t)f64_to_bits(s + y);
+}
+
+// 8 complex entries (limbs of (re, im) pairs) in plane t of the three
+// components x, y and x + y, packed four to a dword.  The residue of the sum
+// comes from the sum of the limb sums (|.| < 2^49): the same value as the
+// residues' sum reduced again, in four operations.
+template <int LIMBS>
+__device__ __forceinline__ void pack_residues_cplx(const Limbs<LIMBS> (&L)[16], int t,
+                                                   const ModTable* __restrict__ tab,
+                                                   uint2 (&w)[3]) {
+  const double p = tab->p[t], ip = tab->inv_p[t], w1 = tab->powL[t][1];
+  uint32_t d[3][2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {             // four entries at a time (registers)
+    uint32_t v[3][4];
+    if (t == 0) {                           // modulus 0 is 256
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        v[0][i] = residue_256_byte<LIMBS>(L[8 * q + 2 * i]);
+        v[1][i] = residue_256_byte<LIMBS>(L[8 * q + 2 * i + 1]);
+        v[2][i] = v[0][i] + v[1][i];
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        double x = L[8 * q + 2 * i].x[0], y = L[8 * q + 2 * i + 1].x[0];
+        if constexpr (LIMBS == 2) {
+          x = fma(L[8 * q + 2 * i].x[1], w1, x);
+          y = fma(L[8 * q + 2 * i + 1].x[1], w1, y);
+        }
+        v[0][i] = residue_of_sum(x, p, ip);
+        v[1][i] = residue_of_sum(y, p, ip);
+        v[2][i] = residue_of_sum(x + y, p, ip);
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) d[c][q] = pack_low_bytes(v[c][0], v[c][1], v[c][2], v[c][3]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int c = 0; c < 3; ++c) w[c] = make_uint2(d[c][0], d[c][1]);
+}
 
 // Block `bx` of `nblocks` of an operand.  mode 0 or 1 (Algorithm 2 or 1).
-// status: set to OZ2_STATUS_NONFINITE for a non-finite squared norm, if given.
-template <typename T, bool CONTIG, bool NT, int LIMBS, bool SPLIT>
+// CPLX: X holds (re, im) pairs, ld and k count pairs, and the planes of
+// component c and modulus t are plane c N + t.  status: set to OZ2_STATUS_NONFINITE for a non-finite squared norm, if given.
+template <typename T, bool CONTIG, bool NT, int LIMBS, bool SPLIT, bool CPLX = false>
 __device__ __forceinline__ void k12_scale_body(
-    const T* __restrict__ X, int64_t ld, int64_t nvec, int64_t k, int mode,
+    const T* __restrict__ X, int64_t ld, int64_t nvec, int64_t k_entries, int mode,
     const ModTable* __restrict__ tab, int N, int32_t* __restrict__ e_out,
     double* __restrict__ S_out, int* __restrict__ status, int8_t* __restrict__ R, int64_t Vp,
     int64_t Kp, const K12Shape sh, int bx, int nblocks) {
-  constexpr int VL = kK12VL<T>, GL = 64 / VL, KB = GL * 16, CPB = KB / kKC;
-  __shared__ double part[kK12Part<VL>];     // [chunk][vector of the block]
+  constexpr int E = CPLX ? 2 : 1;           // components per entry
+  constexpr int VL = CPLX ? kK12VLCplx : kK12VL<T>;
+  constexpr int GL = 64 / VL, KB = GL * 16, CPB = KB / kKC;
+  __shared__ double part[kK12Part<VL, E * kK12MaxK>];   // [chunk][vector of the block]
   __shared__ double pmax[kK12Waves][VL];
   __shared__ int32_t exps[64];
   const int lane = threadIdx.x & 63;
@@ -89,15 +147,16 @@ __device__ __forceinline__ void k12_scale_body(
   const int pw = SPLIT ? sh.pw : 1;
   // Two blocks that share the 128-byte lines of a strided operand run on the
   // same XCD (ids 8 apart), so that its L2 fetches the lines once.
-  if (!CONTIG && VB * (int)sizeof(T) < 128 && (bx | 15) < nblocks)
+  if (!CONTIG && VB * E * (int)sizeof(T) < 128 && (bx | 15) < nblocks)
     bx = (bx & ~15) | ((bx & 7) << 1) | ((bx >> 3) & 1);
   const int64_t vb0 = (int64_t)bx * VB;
   const int vl = vwi * VL + v;
   const int64_t vec = vb0 + vl;
   // Vectors beyond nvec repeat the last one: their rows of the planes only
   // reach products that nothing reads.
-  const T* Xv = X + (vec < nvec ? vec : nvec - 1) * (CONTIG ? ld : 1);
-  const int64_t st = CONTIG ? 1 : ld;       // between entries
+  const T* Xv = X + (vec < nvec ? vec : nvec - 1) * (CONTIG ? E * ld : E);
+  const int64_t st = CONTIG ? 1 : ld;       // between components (pairs, if strided)
+  const int64_t k = E * k_entries;          // components
   const int nkb = (int)((k + KB - 1) / KB);
   const bool on = SPLIT ? pg < pw : wr < sh.vw;   // else this wave has no tile
   const int last = (nkb - 1 - kwi) / sh.kw; // this wave's last block of k
@@ -107,13 +166,27 @@ __device__ __forceinline__ void k12_scale_body(
   auto load = [&](int kb, auto nt) {
     const int h0 = kb * KB + g * 16;
     if ((kb + 1) * KB <= k) {
-      const T* p = Xv + h0 * st;
+      if constexpr (CPLX && !CONTIG) {
+        const T* p = Xv + h0 * st;          // pair h0 / 2, pairs 2 ld apart
 #pragma unroll
-      for (int i = 0; i < 16; ++i) a[i] = load_in<decltype(nt)::value>(p + i * st);
+        for (int i = 0; i < 8; ++i) {
+          typedef T Pair __attribute__((ext_vector_type(2)));
+          const Pair z = *reinterpret_cast<const Pair*>(p + 2 * i * st);
+          a[2 * i] = (double)z[0];
+          a[2 * i + 1] = (double)z[1];
+        }
+      } else {
+        const T* p = Xv + h0 * st;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) a[i] = load_in<decltype(nt)::value>(p + i * st);
+      }
     } else {
       const int kl = (int)k - 1;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) a[i] = (double)Xv[(h0 + i < kl ? h0 + i : kl) * st];
+      for (int i = 0; i < 16; ++i) {
+        const int h = h0 + i < kl ? h0 + i : kl;
+        a[i] = (double)(CPLX && !CONTIG ? Xv[(h & ~1) * st + (h & 1)] : Xv[h * st]);
+      }
 #pragma unroll
       for (int i = 0; i < 16; ++i)
         if (h0 + i > kl) a[i] = 0.0;
@@ -180,7 +253,7 @@ __device__ __forceinline__ void k12_scale_body(
   const bool flagged = e0 == kExpNonFinite;
   const int32_t ev = flagged ? 0 : e0;
   // Conversion, from the last block of entries (still in registers) back.
-  int8_t* out = R + vec * Kp + g * 16;
+  int8_t* out = R + vec * Kp + g * (16 / E);
   const int64_t plane = Vp * Kp;
   for (int it = last; it >= 0; --it) {
     const int kb = it * sh.kw + kwi;
@@ -194,24 +267,34 @@ __device__ __forceinline__ void k12_scale_body(
     Limbs<LIMBS> L[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) L[i] = limbs_of<LIMBS>(trunc(ldexp(a[i], ev)));
-    int8_t* o = out + (int64_t)kb * KB;
+    int8_t* o = out + (int64_t)kb * (KB / E);
     for (int t = pg; t < N; t += pw) {
-      uint32_t w[4];
-      pack_residues<LIMBS, 16>(L, t, tab, w);
-      store_packed<16, NT>(o + t * plane, w);
+      if constexpr (CPLX) {
+        uint2 w[3];
+        pack_residues_cplx<LIMBS>(L, t, tab, w);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) store_out<NT>(o + (c * N + t) * plane, w[c]);
+      } else {
+        uint32_t w[4];
+        pack_residues<LIMBS, 16>(L, t, tab, w);
+        store_packed<16, NT>(o + t * plane, w);
+      }
     }
   }
   // Zeros from there to the padded end of the vector (less than 128 bytes).
-  const int hz = nkb * KB + g * 16;
-  if (kwi == 0 && hz < (int)Kp)
-    for (int t = pg; t < N; t += pw)
-      store_out<NT>(out + t * plane + nkb * KB, make_uint4(0, 0, 0, 0));
+  if constexpr (KB / E < 128) {
+    const int hz = nkb * KB + g * 16;
+    if (kwi == 0 && hz < (int)Kp)
+      for (int t = pg; t < N; t += pw)
+        store_out<NT>(out + t * plane + nkb * KB, make_uint4(0, 0, 0, 0));
+  }
 }
 
 // Both operands in one launch: blocks [0, nA) take the rows of A, the others
 // the columns of B.  Block 0 clears the status word (if given): K4 sets it.
-template <typename T, bool NT, int LIMBS, bool SPLIT>
-__global__ __launch_bounds__(64 * kK12Waves, 4) void k12_scale_ab(
+// (At two blocks per CU the complex form spilled: 872 us for 660.)
+template <typename T, bool NT, int LIMBS, bool SPLIT, bool CPLX = false>
+__global__ __launch_bounds__(64 * kK12Waves, CPLX ? 2 : 4) void k12_scale_ab(
     const T* __restrict__ A, int64_t lda, int64_t m, const T* __restrict__ B, int64_t ldb,
     int64_t n, int64_t k, int mode, const ModTable* __restrict__ tab, int N,
     int32_t* __restrict__ eA, int32_t* __restrict__ eB, double* __restrict__ SA,
@@ -221,10 +304,10 @@ __global__ __launch_bounds__(64 * kK12Waves, 4) void k12_scale_ab(
   int* st = set_status ? status : nullptr;
   if (!set_status && b == 0 && threadIdx.x == 0) status[0] = 0;
   if (b < nA)
-    k12_scale_body<T, false, NT, LIMBS, SPLIT>(A, lda, m, k, mode, tab, N, eA, SA, st, RA, Mp, Kp, sh,
+    k12_scale_body<T, false, NT, LIMBS, SPLIT, CPLX>(A, lda, m, k, mode, tab, N, eA, SA, st, RA, Mp, Kp, sh,
                                            b, nA);
   else
-    k12_scale_body<T, true, NT, LIMBS, SPLIT>(B, ldb, n, k, mode, tab, N, eB, SB, st, RB, Np, Kp, sh,
+    k12_scale_body<T, true, NT, LIMBS, SPLIT, CPLX>(B, ldb, n, k, mode, tab, N, eB, SB, st, RB, Np, Kp, sh,
                                           b - nA, (int)gridDim.x - nA);
 }
 

@@ -331,13 +331,13 @@ void launch_split(const T* A, int64_t lda, const T* B, int64_t ldb, int64_t m, i
 
 // K12 for both operands.  A debug call runs no K4, so its status bit is set
 // by this kernel (behind a launch that clears it).
-template <typename T>
+template <typename T, bool CPLX = false>
 void launch_k12(const T* A, int64_t lda, const T* B, int64_t ldb, int64_t m, int64_t n, int64_t k,
                 const Layout& L, char* ws, const ModTable* tab, int N, int mode, bool dbg) {
   int* status = (int*)(ws + L.status);
   if (dbg) k_clear_status<<<1, 64, 0, g_stream>>>(status);
-  constexpr int VL = kK12VL<T>;
-  K12Shape sh = k12_shape<VL>(L.Kp);
+  constexpr int VL = CPLX ? kK12VLCplx : kK12VL<T>;
+  K12Shape sh = k12_shape<VL>(CPLX ? 2 * L.Kp : L.Kp);
   auto blocks = [&] { return k12_blocks(m, VL, sh) + k12_blocks(n, VL, sh); };
   auto go = [&](auto kernel) {
     kernel<<<(unsigned)blocks(), 64 * kK12Waves, 0, g_stream>>>(
@@ -349,8 +349,8 @@ void launch_k12(const T* A, int64_t lda, const T* B, int64_t ldb, int64_t m, int
   // planes of the same entries instead.
   while (sh.vw > 1 && blocks() < 256) sh.vw /= 2;
   sh.pw = std::min(kK12Waves / (sh.kw * sh.vw), N);
-  if (sh.pw > 1) go(k12_scale_ab<T, false, 2, true>);
-  else go(k12_scale_ab<T, false, 2, false>);
+  if (sh.pw > 1) go(k12_scale_ab<T, false, 2, true, CPLX>);
+  else go(k12_scale_ab<T, false, 2, false, CPLX>);
 }
 
 // K3 over the planes given by (t, planes): EPI 0 runs all N planes (t
@@ -689,9 +689,10 @@ int run_complex(int64_t m, int64_t n, int64_t k, const T* A, int64_t lda, const 
 
   StageClock clk;
   clk.mark(0);
+  const bool k12 = mode != OZ2_MODE_EXACT && HT.limbs == 2 && k <= kK12MaxK;
   // K1: squared norms over the 2k components and exponents.
-  k_clear_status<<<1, 64, 0, g_stream>>>((int*)(ws + L.status));
-  {
+  if (!k12) {
+    k_clear_status<<<1, 64, 0, g_stream>>>((int*)(ws + L.status));
     double* pmA = L.maxA ? (double*)(ws + L.maxA) : nullptr;
     double* pmB = L.maxB ? (double*)(ws + L.maxB) : nullptr;
     dim3 gA((unsigned)((m + 63) / 64), (unsigned)((L.nch + 3) / 4));
@@ -722,7 +723,9 @@ int run_complex(int64_t m, int64_t n, int64_t k, const T* A, int64_t lda, const 
   }
   clk.mark(1);
   // K2: integers and the residues of the three components.
-  {
+  if (k12) {
+    launch_k12<T, true>(A, lda, B, ldb, m, n, k, L, ws, tab, N, mode, false);
+  } else {
     const int64_t gx = L.Mp / kK2CVB;
     const int64_t blocksA = gx * (L.Kp / kK2CHB);
     const int64_t workB = L.Np * (L.Kp / kK2CEPL);
@@ -752,15 +755,17 @@ int run_complex(int64_t m, int64_t n, int64_t k, const T* A, int64_t lda, const 
   // K4: both parts, CRT and unscaling.
   {
     const int64_t blocks = ((m + 31) / 32) * ((n + 31) / 32);
-    const unsigned grid = (unsigned)((blocks + 3) / 4);
+    const int64_t waves = blocks * (HT.slices >= 4 ? kK4CPasses<4> : kK4CPasses<3>);
+    const unsigned grid = (unsigned)((waves + 3) / 4);
     const uint8_t* U = (const uint8_t*)(ws + L.U);
     const int32_t* eA = (const int32_t*)(ws + L.eA);
     const int32_t* eB = (const int32_t*)(ws + L.eB);
+    int* st = k12 ? (int*)(ws + L.status) : nullptr;
     switch (HT.slices) {
-      case 1: k4_crt_cplx<1, T><<<grid, 256, 0, g_stream>>>(U, eA, eB, tab, N, m, n, L.Mp, L.Np, C, ldc); break;
-      case 2: k4_crt_cplx<2, T><<<grid, 256, 0, g_stream>>>(U, eA, eB, tab, N, m, n, L.Mp, L.Np, C, ldc); break;
-      case 3: k4_crt_cplx<3, T><<<grid, 256, 0, g_stream>>>(U, eA, eB, tab, N, m, n, L.Mp, L.Np, C, ldc); break;
-      default: k4_crt_cplx<4, T><<<grid, 256, 0, g_stream>>>(U, eA, eB, tab, N, m, n, L.Mp, L.Np, C, ldc); break;
+      case 1: k4_crt_cplx<1, T><<<grid, 256, 0, g_stream>>>(U, eA, eB, tab, N, m, n, L.Mp, L.Np, C, ldc, st); break;
+      case 2: k4_crt_cplx<2, T><<<grid, 256, 0, g_stream>>>(U, eA, eB, tab, N, m, n, L.Mp, L.Np, C, ldc, st); break;
+      case 3: k4_crt_cplx<3, T><<<grid, 256, 0, g_stream>>>(U, eA, eB, tab, N, m, n, L.Mp, L.Np, C, ldc, st); break;
+      default: k4_crt_cplx<4, T><<<grid, 256, 0, g_stream>>>(U, eA, eB, tab, N, m, n, L.Mp, L.Np, C, ldc, st); break;
     }
   }
   clk.mark(4);

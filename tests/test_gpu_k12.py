@@ -38,3 +38,21 @@ def test_binary32_operands(m, n, k):
     A, B = (x.astype(np.float32) for x in inputs.problem(m, n, k, 0.5, seed=k))
     want = ref.sgemm(A, B, 7)
     assert np.array_equal(_gpu_sgemm(A, B, 7).view(np.uint32), want.view(np.uint32))
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("m,n,k,single", [
+    (1, 5, 1, False), (5, 33, 31, False), (33, 4, 32, True), (3, 65, 127, True),
+    (65, 31, 128, False), (9, 7, 129, True), (4, 3, 1025, False), (2, 3, 4096, False),
+    (3, 2, 4097, True)])
+def test_complex_operands(m, n, k, single, mode):
+    """Complex operands through the same kernel: blocks of 128 entries, norms
+    over 2k components, three components' planes."""
+    from oracle import complex as zref
+    from test_gpu_complex import _gpu, _same
+    N = 6 if single else 9 + (m + k) % 12
+    A, B = inputs.complex_problem(m, n, k, 1.0, seed=m + k)
+    if single:
+        A, B = A.astype(np.complex64), B.astype(np.complex64)
+    want = (zref.cgemm if single else zref.zgemm)(A, B, N, mode)
+    assert _same(_gpu(A, B, N, mode, lda=m + 2, ldb=k + 1, ldc=m + 3, single=single), want)
