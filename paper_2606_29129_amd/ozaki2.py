@@ -272,7 +272,8 @@ def ozaki2_debug_log2f(x, y, n):
 
 # --- torch conveniences ------------------------------------------------------
 
-_workspaces = {}   # device index -> (uint8 tensor, 256-aligned address, usable bytes)
+# device index -> (uint8 tensor, 256-aligned address, usable bytes, streams it was used on)
+_workspaces = {}
 
 
 def ensure_workspace(nbytes, device=None):
@@ -282,15 +283,21 @@ def ensure_workspace(nbytes, device=None):
     never allocates device memory (its default workspace policy); this is
     where the conveniences below get theirs.  Returns the address."""
     import torch
-    dev = torch.device("cuda", torch.cuda.current_device()) if device is None else torch.device(device)
-    idx = dev.index if dev.index is not None else torch.cuda.current_device()
+    idx = None if device is None else torch.device(device).index
+    if idx is None:
+        idx = torch.cuda.current_device()
     cur = _workspaces.get(idx)
     if cur is None or cur[2] < nbytes:
-        t = torch.empty(max(int(nbytes), 1) + 256, dtype=torch.uint8, device=dev)
-        cur = (t, (t.data_ptr() + 255) // 256 * 256, max(int(nbytes), 1))
+        t = torch.empty(max(int(nbytes), 1) + 256, dtype=torch.uint8,
+                        device=torch.device("cuda", idx))
+        cur = (t, (t.data_ptr() + 255) // 256 * 256, max(int(nbytes), 1), set())
         _workspaces[idx] = cur
-    # the tensor is used on the current stream from here on
-    cur[0].record_stream(torch.cuda.current_stream(dev))
+    # the tensor is used on the current stream from here on (the allocator
+    # keeps a stream once told, until the tensor is freed)
+    stream = torch._C._cuda_getCurrentRawStream(idx)
+    if stream not in cur[3]:
+        cur[0].record_stream(torch.cuda.current_stream(idx))
+        cur[3].add(stream)
     _check("ozaki2_set_workspace", ozaki2_set_workspace(cur[1], cur[2]))
     return cur[1]
 
@@ -305,7 +312,8 @@ def _mode(mode):
 
 
 def _bind_current_stream(torch):
-    ozaki2_set_stream(torch.cuda.current_stream().cuda_stream)
+    # the raw handle of torch.cuda.current_stream(), without building the object
+    ozaki2_set_stream(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
 
 
 def dgemm(A, B, N=14, mode="revised", out=None):
