@@ -240,10 +240,12 @@ __global__ __launch_bounds__(256) void k1_fold(
 // a non-finite one gets kExpNonFinite and sets the status bit.
 constexpr int32_t kExpZero = INT32_MIN + 1;
 
-__global__ __launch_bounds__(256) void k1_fold_first(
+__device__ __forceinline__ void k1_fold_first_body(
     const double* __restrict__ part, const double* __restrict__ pmax, int64_t nchunks,
-    int64_t nvec, int32_t* __restrict__ e1_out, int* __restrict__ status) {
-  const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    int64_t nvec, int64_t Vp, int32_t* __restrict__ e1_out, int32_t* __restrict__ cmax,
+    int* __restrict__ status, int64_t bx) {
+  const int64_t v = bx * 256 + threadIdx.x;
+  if (v < Vp) cmax[v] = 0;   // the bound product's maxima start at 0
   if (v >= nvec) return;
   double S, mx;
   fold_chunks(part, pmax, nchunks, nvec, v, &S, &mx);
@@ -260,12 +262,26 @@ __global__ __launch_bounds__(256) void k1_fold_first(
   e1_out[v] = e;
 }
 
+// Both operands: blocks [0, nA) for the rows of A (padded: Mp), the rest for
+// the columns of B.
+__global__ __launch_bounds__(256) void k1_fold_first_ab(
+    const double* __restrict__ partA, const double* __restrict__ maxA, int64_t m, int64_t Mp,
+    int32_t* __restrict__ e1A, int32_t* __restrict__ cmaxA, const double* __restrict__ partB,
+    const double* __restrict__ maxB, int64_t n, int64_t Np, int32_t* __restrict__ e1B,
+    int32_t* __restrict__ cmaxB, int64_t nchunks, int* __restrict__ status, int64_t nA) {
+  const int64_t b = blockIdx.x;
+  if (b < nA) k1_fold_first_body(partA, maxA, nchunks, m, Mp, e1A, cmaxA, status, b);
+  else k1_fold_first_body(partB, maxB, nchunks, n, Np, e1B, cmaxB, status, b - nA);
+}
+
 // Accurate mode, final exponent: log2 mu = e' + floor(P'_accu - RU32(delta *
 // tilde-log2(max_h cbar))) (the accurate-mode formula of Section 2.3).
-__global__ __launch_bounds__(256) void k1_accurate_exponent(
+// No squared norms in this mode: zeros are reported.
+__device__ __forceinline__ void k1_accurate_exponent_body(
     const int32_t* __restrict__ e1, const int32_t* __restrict__ cmax, int64_t nvec,
-    const ModTable* __restrict__ tab, int32_t* __restrict__ e_out) {
-  const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const ModTable* __restrict__ tab, int32_t* __restrict__ e_out, double* __restrict__ S_out,
+    int64_t bx) {
+  const int64_t v = bx * 256 + threadIdx.x;
   if (v >= nvec) return;
   const int32_t a = e1[v];
   int32_t e;
@@ -273,11 +289,17 @@ __global__ __launch_bounds__(256) void k1_accurate_exponent(
   else if (a == kExpZero) e = 0;
   else e = accurate_exponent(a, (int64_t)cmax[v], tab->p_prop, tab->delta);
   e_out[v] = e;
+  S_out[v] = 0.0;
 }
 
-__global__ void k_fill_i32(int32_t* __restrict__ p, int64_t n, int32_t v) {
-  int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) p[i] = v;
+__global__ __launch_bounds__(256) void k1_accurate_exponent_ab(
+    const int32_t* __restrict__ e1A, const int32_t* __restrict__ cmaxA, int64_t m,
+    int32_t* __restrict__ eA, double* __restrict__ SA, const int32_t* __restrict__ e1B,
+    const int32_t* __restrict__ cmaxB, int64_t n, int32_t* __restrict__ eB,
+    double* __restrict__ SB, const ModTable* __restrict__ tab, int64_t nA) {
+  const int64_t b = blockIdx.x;
+  if (b < nA) k1_accurate_exponent_body(e1A, cmaxA, m, tab, eA, SA, b);
+  else k1_accurate_exponent_body(e1B, cmaxB, n, tab, eB, SB, b - nA);
 }
 
 // Status word reset at the start of each call (a kernel, not a memset, so

@@ -296,14 +296,14 @@ OZ2_HD int8_t bar_value(double a, int32_t e) {
 // Bar plane of the strided operand: the geometry of k2_split_strided (VB
 // vectors x (256 / VB) 16 entries per block, one LDS staging pass).
 template <typename T, int VB = kK2VB>
-__global__ __launch_bounds__(256) void k2_bar_strided(
+__device__ __forceinline__ void k2_bar_strided_body(
     const T* __restrict__ X, int64_t ld, int64_t nvec, int64_t k,
-    const int32_t* __restrict__ e, int8_t* __restrict__ R, int64_t Vp, int64_t Kp) {
+    const int32_t* __restrict__ e, int8_t* __restrict__ R, int64_t Kp, int64_t bx, int64_t by) {
   constexpr int G = 256 / VB, HB = G * 16;
   __shared__ uint4 stage[VB][G + 1];
   const int vl = threadIdx.x % VB, g = threadIdx.x / VB;
-  const int64_t v0 = (int64_t)blockIdx.x * VB, v = v0 + vl;
-  const int64_t h0 = (int64_t)blockIdx.y * HB + g * 16;
+  const int64_t v0 = bx * VB, v = v0 + vl;
+  const int64_t h0 = by * HB + g * 16;
   const int32_t ev = v < nvec ? e[v] : kExpZero;
   double a[16];
 #pragma unroll
@@ -320,18 +320,18 @@ __global__ __launch_bounds__(256) void k2_bar_strided(
   stage[vl][g] = make_uint4(w[0], w[1], w[2], w[3]);
   __syncthreads();
   const int orow = threadIdx.x / G, ochunk = threadIdx.x % G;
-  *reinterpret_cast<uint4*>(R + (v0 + orow) * Kp + (int64_t)blockIdx.y * HB + ochunk * 16) =
+  *reinterpret_cast<uint4*>(R + (v0 + orow) * Kp + by * HB + ochunk * 16) =
       stage[orow][ochunk];
 }
 
 // Bar plane of the contiguous operand: one lane per kK2EPT consecutive
 // entries, as k2_split_contig.
 template <typename T, int EPT = kK2EPT>
-__global__ __launch_bounds__(256) void k2_bar_contig(
+__device__ __forceinline__ void k2_bar_contig_body(
     const T* __restrict__ X, int64_t ld, int64_t nvec, int64_t k,
-    const int32_t* __restrict__ e, int8_t* __restrict__ R, int64_t Vp, int64_t Kp) {
+    const int32_t* __restrict__ e, int8_t* __restrict__ R, int64_t Vp, int64_t Kp, int64_t bx) {
   const int64_t groups = Kp / EPT;
-  const int64_t gi = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t gi = bx * 256 + threadIdx.x;
   if (gi >= Vp * groups) return;
   const int64_t v = gi / groups;
   const int64_t h0 = (gi - v * groups) * EPT;
@@ -349,6 +349,19 @@ __global__ __launch_bounds__(256) void k2_bar_contig(
     w[q] = b;
   }
   store_packed<EPT>(R + v * Kp + h0, w);
+}
+
+// Both bar planes in one launch: blocks [0, nA) the strided body's for A (nA =
+// gAx x Kp / kK2HB, gAx = Mp / kK2VB), the others the contiguous one's for B.
+template <typename T>
+__global__ __launch_bounds__(256) void k2_bar_ab(
+    const T* __restrict__ A, int64_t lda, int64_t m, const int32_t* __restrict__ eA,
+    int8_t* __restrict__ barA, const T* __restrict__ B, int64_t ldb, int64_t n,
+    const int32_t* __restrict__ eB, int8_t* __restrict__ barB, int64_t Np, int64_t k, int64_t Kp,
+    int64_t gAx, int64_t nA) {
+  const int64_t b = blockIdx.x;
+  if (b < nA) k2_bar_strided_body<T>(A, lda, m, k, eA, barA, Kp, b % gAx, b / gAx);
+  else k2_bar_contig_body<T>(B, ldb, n, k, eB, barB, Np, Kp, b - nA);
 }
 
 }  // namespace oz2

@@ -510,31 +510,24 @@ int run_gemm(int64_t m, int64_t n, int64_t k, const T* A, int64_t lda, const T* 
       // matrices, one INT8 GEMM reduced to row/column maxima, exponents.
       int32_t* e1A = (int32_t*)(ws + L.e1A);
       int32_t* e1B = (int32_t*)(ws + L.e1B);
-      k1_fold_first<<<(unsigned)((m + 255) / 256), 256, 0, g_stream>>>(
-          (double*)(ws + L.partA), pmA, L.nch, m, e1A, (int*)(ws + L.status));
-      k1_fold_first<<<(unsigned)((n + 255) / 256), 256, 0, g_stream>>>(
-          (double*)(ws + L.partB), pmB, L.nch, n, e1B, (int*)(ws + L.status));
-      dim3 gb((unsigned)(L.Mp / kK2VB), (unsigned)(L.Kp / kK2HB));
-      k2_bar_strided<T><<<gb, 256, 0, g_stream>>>(A, lda, m, k, e1A, (int8_t*)(ws + L.barA),
-                                                  L.Mp, L.Kp);
-      int64_t wb = L.Np * (L.Kp / kK2EPT);
-      k2_bar_contig<T><<<(unsigned)((wb + 255) / 256), 256, 0, g_stream>>>(
-          B, ldb, n, k, e1B, (int8_t*)(ws + L.barB), L.Np, L.Kp);
       int32_t* cmA = (int32_t*)(ws + L.cmaxA);
       int32_t* cmB = (int32_t*)(ws + L.cmaxB);
-      k_fill_i32<<<(unsigned)((L.Mp + 255) / 256), 256, 0, g_stream>>>(cmA, L.Mp, 0);
-      k_fill_i32<<<(unsigned)((L.Np + 255) / 256), 256, 0, g_stream>>>(cmB, L.Np, 0);
+      int64_t fA = (L.Mp + 255) / 256, fB = (L.Np + 255) / 256;
+      k1_fold_first_ab<<<(unsigned)(fA + fB), 256, 0, g_stream>>>(
+          (double*)(ws + L.partA), pmA, m, L.Mp, e1A, cmA, (double*)(ws + L.partB), pmB, n, L.Np,
+          e1B, cmB, L.nch, (int*)(ws + L.status), fA);
+      const int64_t gAx = L.Mp / kK2VB, bA = gAx * (L.Kp / kK2HB);
+      const int64_t bB = (L.Np * (L.Kp / kK2EPT) + 255) / 256;
+      k2_bar_ab<T><<<(unsigned)(bA + bB), 256, 0, g_stream>>>(
+          A, lda, m, e1A, (int8_t*)(ws + L.barA), B, ldb, n, e1B, (int8_t*)(ws + L.barB), L.Np, k,
+          L.Kp, gAx, bA);
       launch_gemm<2>(cfg, (const int8_t*)(ws + L.barA), (const int8_t*)(ws + L.barB), nullptr,
                      cmA, cmB, m, n, L, tab, 0, 1);
-      k1_accurate_exponent<<<(unsigned)((m + 255) / 256), 256, 0, g_stream>>>(
-          e1A, cmA, m, tab, (int32_t*)(ws + L.eA));
-      k1_accurate_exponent<<<(unsigned)((n + 255) / 256), 256, 0, g_stream>>>(
-          e1B, cmB, n, tab, (int32_t*)(ws + L.eB));
-      // no squared norms in this mode: report zeros
-      k_fill_i32<<<(unsigned)((2 * m + 255) / 256), 256, 0, g_stream>>>((int32_t*)(ws + L.SA),
-                                                                         2 * m, 0);
-      k_fill_i32<<<(unsigned)((2 * n + 255) / 256), 256, 0, g_stream>>>((int32_t*)(ws + L.SB),
-                                                                         2 * n, 0);
+      fA = (m + 255) / 256;
+      fB = (n + 255) / 256;
+      k1_accurate_exponent_ab<<<(unsigned)(fA + fB), 256, 0, g_stream>>>(
+          e1A, cmA, m, (int32_t*)(ws + L.eA), (double*)(ws + L.SA), e1B, cmB, n,
+          (int32_t*)(ws + L.eB), (double*)(ws + L.SB), tab, fA);
     }
   }
   clk.mark(1);
