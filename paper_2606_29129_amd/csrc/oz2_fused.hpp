@@ -24,8 +24,8 @@
 // Two waves per SIMD (at most 128 accumulators each) rather than one with all
 // moduli of 16 vectors: alone on its SIMD a wave issues an operation at best
 // every 5.3 cycles, and a dependent binary64 one every 11 (two waves: 5.9).
-// 65536 x 64 x 4096, N = 14: 1.08 ms (1.28 with one wave per SIMD), 2.15 GB
-// read at 2.0 TB/s; the transposed shape 1.09 ms (2.0 ms in the separate
+// 65536 x 64 x 4096, N = 14: 1.05 ms (1.28 with one wave per SIMD), 2.15 GB
+// read at 2.0 TB/s; the transposed shape 1.00 ms (2.0 ms in the separate
 // kernels).
 #pragma once
 
