@@ -212,27 +212,24 @@ OZ2_HD double crt_unscale(const double (&acc)[S], const ModTable& T, int32_t E) 
   double R[S];
 #pragma unroll
   for (int s = 0; s < S; ++s) R[s] = fma(-Q, T.P[s], acc[s]);
+  // The rounded value r of R is within a factor 1 +- 2^-50 of R, so |r| <=
+  // quarterP (< P/4 (1 - 2^-30)) proves |R| < P/2, i.e. R = C''.  (All S
+  // slices count: a kernel whose S exceeds the table's own slice count, such
+  // as the batch's, makes the same decision.)
+  double r = slices_value(R);
   // The common case, about 40 operations against 80 below: R is C'' without a
-  // doubt and the result is normal.  h = R_{S-1} 2^39 + R_{S-2} is R in units
-  // of 2^(39 (S-2)) within 2^14 + 1 and a rounding, so |h| <= fastH shows |R| <
-  // P/2; and |C''| >= 1 (or 0) puts |C| above 2^-E.  (8192 x 8192 outputs, N =
-  // 14: 380 -> 340 us, 1.48 GB at 4.3 TB/s, near a plain copy's 4.6; 16384 x
-  // 16384, N = 17: 1.75 -> 1.70 ms; complex 4096 x 4096 402 -> 378 us.)
+  // doubt and the result is normal (|C''| >= 1, or 0, puts |C| above 2^-E).
+  // (8192 x 8192 outputs, N = 14: 380 -> 340 us, 1.48 GB at 4.3 TB/s, near a
+  // plain copy's 4.6; 16384 x 16384, N = 17: 1.75 -> 1.70 ms; complex 4096 x
+  // 4096 402 -> 378 us.)
   if constexpr (S >= 2) {
-    const double h = fma(R[S - 1], sconst(0x1p39), R[S - 2]);
-    if (fabs(h) <= T.fastH && E <= -(EMIN_Q + PREC - 1)) {
-      double D[S];
-#pragma unroll
-      for (int s = 0; s < S; ++s) D[s] = R[s];
-      normalize(D);
-      return round_signed<S, PREC>(D, E);
+    if (fabs(r) <= T.quarterP && E <= -(EMIN_Q + PREC - 1)) {
+      normalize(R);
+      return round_signed<S, PREC>(R, E);
     }
   }
   // Bring R into (-P/2, P/2): R = C'' + jP with |j| <= 1 and |C''| < P/2.
-  // Fast test first: the rounded value r of R is within a factor 1 +- 2^-50
-  // of R, so |r| <= quarterP (< P/4 (1 - 2^-30)) proves |R| < P/2, i.e.
-  // R = C''.  Otherwise the exact comparisons with P/2 decide.
-  double r = slices_value(R);
+  // Where r leaves a doubt the exact comparisons with P/2 decide.
   if (!(fabs(r) <= T.quarterP)) {
     double D[S];
 #pragma unroll

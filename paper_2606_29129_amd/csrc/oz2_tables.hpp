@@ -32,7 +32,6 @@ struct ModTable {
   double H[kMaxSlices];            // P/2 in 39-bit slices
   double invP;                     // RN(1/P), only for quotient estimates
   double quarterP;                 // a binary64 value a little below P/4
-  double fastH;                    // P/4 in units of 2^(39 (slices - 2)), less 2^15 and a little
   double pm1_rd;                   // RD64(P - 1): x <= P - 1 iff x <= pm1_rd (binary64 x)
   float p_prop;                    // P'_prop = RD32(log2(P-1)/2 - 0.5)
   float p_fast;                    // P'_fast = RD32(log2(P-1)/2 - 1.5)
@@ -179,7 +178,6 @@ inline bool build_table(int N, bool accurate_limbs, ModTable* T) {
   T->log2P = (double)log2P;
   T->invP = (double)exp2l(-log2P);
   T->quarterP = (double)(exp2l(log2P - 2.0L) * (1.0L - 0x1p-30L));
-  T->fastH = ldexp(T->quarterP, -kSliceBits * (T->slices - 2)) - 0x1p15;
   {
     // P - 1 rounded down to binary64: its top 53 bits, truncated.
     const Big Pm1 = P.sub_small(1);
