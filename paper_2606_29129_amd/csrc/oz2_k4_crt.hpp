@@ -12,7 +12,7 @@
 // The quotient Q = round(X / P) (|Q| < 2^14) is estimated from a rounded X; every
 // R_s = Acc_s - Q P_s is exact, and an exact signed comparison with P/2
 // corrects a quotient that is off by one (skipped when a rounded value of R
-// already shows |R| < P/4).  That rounded value also gives the sign; the
+// already shows |R| < P/2).  That rounded value also gives the sign; the
 // magnitude's slices are normalised (carries propagated exactly) and rounded
 // once, to nearest even, at the bit position that the output format
 // (binary64 or binary32, subnormals included) dictates: for normal results by
@@ -213,9 +213,12 @@ OZ2_HD double crt_unscale(const double (&acc)[S], const ModTable& T, int32_t E) 
 #pragma unroll
   for (int s = 0; s < S; ++s) R[s] = fma(-Q, T.P[s], acc[s]);
   // The rounded value r of R is within a factor 1 +- 2^-50 of R, so |r| <=
-  // quarterP (< P/4 (1 - 2^-30)) proves |R| < P/2, i.e. R = C''.  (All S
-  // slices count: a kernel whose S exceeds the table's own slice count, such
-  // as the batch's, makes the same decision.)
+  // halfP (P/2 (1 - 2^-30)) proves |R| < P/2, i.e. R = C''.  (All S slices
+  // count: a kernel whose S exceeds the table's own slice count, such as the
+  // batch's, makes the same decision.)  The bound is as near to P/2 as that
+  // allows: where k is 1 the scaling puts most |C''| between P/8 and P/2, and
+  // with P/4 a wave took both paths (binary32 8192 x 8192, k = 1, N = 7, whole
+  // call: 504 us, 366 now; binary64, N = 14: 773, 666).
   double r = slices_value(R);
   // The common case, about 40 operations against 80 below: R is C'' without a
   // doubt and the result is normal (|C''| >= 1, or 0, puts |C| above 2^-E).
@@ -223,14 +226,14 @@ OZ2_HD double crt_unscale(const double (&acc)[S], const ModTable& T, int32_t E) 
   // plain copy's 4.6; 16384 x 16384, N = 17: 1.75 -> 1.70 ms; complex 4096 x
   // 4096 402 -> 378 us.)
   if constexpr (S >= 2) {
-    if (fabs(r) <= T.quarterP && E <= -(EMIN_Q + PREC - 1)) {
+    if (fabs(r) <= T.halfP && E <= -(EMIN_Q + PREC - 1)) {
       normalize(R);
       return round_signed<S, PREC>(R, E);
     }
   }
   // Bring R into (-P/2, P/2): R = C'' + jP with |j| <= 1 and |C''| < P/2.
   // Where r leaves a doubt the exact comparisons with P/2 decide.
-  if (!(fabs(r) <= T.quarterP)) {
+  if (!(fabs(r) <= T.halfP)) {
     double D[S];
 #pragma unroll
     for (int s = 0; s < S; ++s) D[s] = R[s] - T.H[s];

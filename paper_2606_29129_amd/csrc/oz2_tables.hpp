@@ -31,7 +31,7 @@ struct ModTable {
   double P[kMaxSlices];            // P in 39-bit slices
   double H[kMaxSlices];            // P/2 in 39-bit slices
   double invP;                     // RN(1/P), only for quotient estimates
-  double quarterP;                 // a binary64 value a little below P/4
+  double halfP;                    // a binary64 value a little below P/2
   double pm1_rd;                   // RD64(P - 1): x <= P - 1 iff x <= pm1_rd (binary64 x)
   float p_prop;                    // P'_prop = RD32(log2(P-1)/2 - 0.5)
   float p_fast;                    // P'_fast = RD32(log2(P-1)/2 - 1.5)
@@ -177,7 +177,7 @@ inline bool build_table(int N, bool accurate_limbs, ModTable* T) {
   long double log2P = P.log2l_approx();
   T->log2P = (double)log2P;
   T->invP = (double)exp2l(-log2P);
-  T->quarterP = (double)(exp2l(log2P - 2.0L) * (1.0L - 0x1p-30L));
+  T->halfP = (double)(exp2l(log2P - 1.0L) * (1.0L - 0x1p-30L));
   {
     // P - 1 rounded down to binary64: its top 53 bits, truncated.
     const Big Pm1 = P.sub_small(1);

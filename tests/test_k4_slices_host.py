@@ -8,6 +8,7 @@ import shutil
 import struct
 import subprocess
 import tempfile
+from fractions import Fraction
 
 import pytest
 
@@ -49,3 +50,16 @@ def test_four_slices_for_every_table(driver, N):
     assert len(got) == len(want)
     bad = [(cases[i // 2], hex(g), hex(w)) for i, (g, w) in enumerate(zip(got, want)) if g != w]
     assert not bad, (len(bad), bad[:4])
+
+
+def test_fast_bound_is_just_below_half_of_P(driver):
+    """The fast test accepts |C''| up to P/2 (1 - 2^-30): safely below P/2,
+    and above what the scaling can leave (its binary32 constants stay about
+    2^-21 below P/2, relatively), so that small k does not miss it."""
+    out = subprocess.run([driver, "bounds"], capture_output=True, text=True, check=True).stdout
+    got = [Fraction(float.fromhex(x)) for x in out.split()]
+    assert len(got) == 19
+    for N, b in zip(range(2, 21), got):
+        P = constants.step1(N)[1]
+        assert Fraction(P, 2) * (1 - Fraction(1, 2 ** 29)) < b
+        assert b < Fraction(P, 2) * (1 - Fraction(1, 2 ** 31))
