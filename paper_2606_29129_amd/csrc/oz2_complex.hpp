@@ -304,6 +304,7 @@ __global__ __launch_bounds__(256) void k4_crt_cplx(
 #pragma unroll
       for (int q = 0; q < RW; ++q) w[c][q] = nx[c][q];
   }
+  bool bad = bi == 0 && f == kExpNonFinite;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int lr = acc_row(R * h + r, lane);   // RPW h .. RPW h + RPW - 1
@@ -312,9 +313,9 @@ __global__ __launch_bounds__(256) void k4_crt_cplx(
     out.x = out.y = (TO)0;
     if (row < m && col < n) {
       const int32_t e = eA[row];
+      bad = bad || (bj == 0 && e == kExpNonFinite);
       if (e == kExpNonFinite || f == kExpNonFinite) {
         out.x = out.y = (TO)__builtin_nan("");
-        if (status) atomicOr(status, 1);       // where no earlier kernel could set it
       } else {
         double a[S], b[S];
 #pragma unroll
@@ -333,6 +334,7 @@ __global__ __launch_bounds__(256) void k4_crt_cplx(
     }
     tile[wave][lr - RPW * h][lc] = out;
   }
+  k4_set_status(status, bad);
   // LDS operations of one wave complete in order; the fence keeps the
   // compiler from moving the reads above the writes.
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
