@@ -32,12 +32,13 @@ namespace oz2 {
 
 constexpr double kTuneMargin = 4.0;
 constexpr int64_t kPhiSample = int64_t(1) << 20;   // entries per operand
-constexpr int kStatBlocks = 16;                     // blocks per operand
-// In a batch, whose launch otherwise ends with the 16 blocks of its largest
-// operands (64 problems, sides 64..2048: 279 us, 196 with 64 blocks each; 32
-// make the call as fast and half the partials to copy back).  A single
-// estimate keeps 16: its partials fit the first KiB of the workspace.
-constexpr int kStatBlocksBatch = 32;
+// Blocks per operand, the same for a single estimate and for a batch's, so
+// that both add the same partial sums and give the same phi.  A batch's
+// launch ends with the blocks of its largest operands (64 problems, sides
+// 64..2048: 279 us with 16 blocks, 196 with 64; with 32 the call is as fast
+// and the partials to copy back are half); 32 is also the most whose scratch
+// leaves a single estimate in the first KiB of the workspace.
+constexpr int kStatBlocks = 32;
 
 // Envelope at grid point (ik, ip) for the j-th tabulated N: the largest
 // tabulated error at or below the grid point, for this N or a larger one.
@@ -146,7 +147,7 @@ __device__ __forceinline__ void vec_logsums(GlobalDouble* X, const StatSrc& s, i
 // Per-block partial sums of the pooled within-vector statistics of one
 // operand: W = sum over vectors of sum (log|x| - mean of the vector)^2 and
 // D = sum over vectors of (count - 1), vectors with fewer than two entries
-// left out.  Block b covers operand b / nb, nb blocks each; the host adds the
+// left out.  Block b covers operand b / kStatBlocks; the host adds the
 // partials of an operand in block order (deterministic).  Strided vectors
 // (rows of a column-major matrix): kStatRows consecutive vectors per pass of
 // a block, the block's threads split into kStatSegs groups that take
@@ -157,10 +158,10 @@ __device__ __forceinline__ void vec_logsums(GlobalDouble* X, const StatSrc& s, i
 // across the wave.
 constexpr int kStatSegs = 16, kStatRows = 256 / kStatSegs;
 __global__ __launch_bounds__(256) void k_logstats(const StatSrc* __restrict__ src,
-                                                  double* __restrict__ part, int nb) {
+                                                  double* __restrict__ part) {
   __shared__ double red[2][256];
   __shared__ double ws[3][kStatSegs][kStatRows];
-  const int op = blockIdx.x / nb, sub = blockIdx.x % nb;
+  const int op = blockIdx.x / kStatBlocks, sub = blockIdx.x % kStatBlocks;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const StatSrc s = src[op];
   // The operand pointer comes from a descriptor, so the compiler cannot tell
@@ -172,7 +173,7 @@ __global__ __launch_bounds__(256) void k_logstats(const StatSrc* __restrict__ sr
     const int r = tid % kStatRows, sg = tid / kStatRows;
     const int64_t q = (s.len + kStatSegs - 1) / kStatSegs;
     const int64_t e0 = sg * q, e1 = e0 + q < s.len ? e0 + q : s.len;
-    for (int64_t g = sub; g * kStatRows < s.nvec; g += nb) {
+    for (int64_t g = sub; g * kStatRows < s.nvec; g += kStatBlocks) {
       const int64_t v = g * kStatRows + r;
       double n = 0.0, s1 = 0.0, s2 = 0.0;
       if (v < s.nvec) vec_logsums(X, s, v, e0, e1, 1, &n, &s1, &s2);
@@ -193,7 +194,7 @@ __global__ __launch_bounds__(256) void k_logstats(const StatSrc* __restrict__ sr
       __syncthreads();
     }
   } else {
-    for (int64_t v = (int64_t)sub * 4 + wave; v < s.nvec; v += (int64_t)nb * 4) {
+    for (int64_t v = (int64_t)sub * 4 + wave; v < s.nvec; v += (int64_t)kStatBlocks * 4) {
       double n, s1, s2;
       vec_logsums(X, s, v, lane, s.len, 64, &n, &s1, &s2);
       for (int o = 32; o > 0; o >>= 1) {
@@ -217,15 +218,15 @@ __global__ __launch_bounds__(256) void k_logstats(const StatSrc* __restrict__ sr
     }
     __syncthreads();
   }
-  if (tid < 2) part[((int64_t)op * nb + sub) * 2 + tid] = red[tid][0];
+  if (tid < 2) part[((int64_t)op * kStatBlocks + sub) * 2 + tid] = red[tid][0];
 }
 
 // phi from the partials of one operand: sqrt(max(var - 1, 0)) with var =
 // W / D the pooled within-vector sample variance of log|x|; 0 when no vector
 // has two entries.
-inline double phi_from_partials(const double* p, int nb) {
+inline double phi_from_partials(const double* p) {
   double W = 0.0, D = 0.0;
-  for (int b = 0; b < nb; ++b) {
+  for (int b = 0; b < kStatBlocks; ++b) {
     W += p[2 * b];
     D += p[2 * b + 1];
   }

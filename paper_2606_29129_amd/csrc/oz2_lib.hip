@@ -801,33 +801,34 @@ void batch_release() {
 // Scratch of the phi estimate (operand descriptors and per-block partial
 // statistics) for `ns` operands; it sits right after the status word of the
 // workspace.
-size_t tune_scratch_bytes(size_t ns, int nb) {
-  return align256(sizeof(StatSrc) * ns) + align256(sizeof(double) * 2 * nb * ns);
+size_t tune_scratch_bytes(size_t ns) {
+  return align256(sizeof(StatSrc) * ns) + align256(sizeof(double) * 2 * kStatBlocks * ns);
 }
+// A single estimate uses the first KiB of the workspace (status included).
+static_assert(256 + 256 + sizeof(double) * 2 * kStatBlocks <= 1024 && sizeof(StatSrc) <= 256,
+              "scratch of ozaki2_estimate_phi");
 
 // phi of each operand (pooled within-vector variance of log|x|,
 // oz2_autotune.hpp): one
 // launch for all of them on the library stream into the workspace scratch
 // at `scratch`, then a synchronising copy of the per-block partials.
-int estimate_phis(char* scratch, const std::vector<StatSrc>& srcs, int nb,
-                  std::vector<double>* phis) {
+int estimate_phis(char* scratch, const std::vector<StatSrc>& srcs, std::vector<double>* phis) {
   const size_t ns = srcs.size();
   phis->assign(ns, 0.0);
   if (ns == 0) return 0;
   const size_t off_part = align256(sizeof(StatSrc) * ns);
-  std::vector<double> part(2 * (size_t)nb * ns);
+  std::vector<double> part(2 * kStatBlocks * ns);
   if (hipMemcpyAsync(scratch, srcs.data(), sizeof(StatSrc) * ns, hipMemcpyHostToDevice,
                      g_stream) != hipSuccess)
     return OZ2_ERR_HIP;
-  k_logstats<<<(unsigned)(ns * nb), 256, 0, g_stream>>>(
-      reinterpret_cast<const StatSrc*>(scratch), reinterpret_cast<double*>(scratch + off_part),
-      nb);
+  k_logstats<<<(unsigned)(ns * kStatBlocks), 256, 0, g_stream>>>(
+      reinterpret_cast<const StatSrc*>(scratch), reinterpret_cast<double*>(scratch + off_part));
   if (hipGetLastError() != hipSuccess ||
       hipMemcpyAsync(part.data(), scratch + off_part, sizeof(double) * part.size(),
                      hipMemcpyDeviceToHost, g_stream) != hipSuccess ||
       hipStreamSynchronize(g_stream) != hipSuccess)
     return OZ2_ERR_HIP;
-  for (size_t i = 0; i < ns; ++i) (*phis)[i] = phi_from_partials(part.data() + 2 * (size_t)nb * i, nb);
+  for (size_t i = 0; i < ns; ++i) (*phis)[i] = phi_from_partials(part.data() + 2 * kStatBlocks * i);
   return 0;
 }
 
@@ -926,7 +927,7 @@ int plan_batch(int batch, const oz2_problem* P, int mode, size_t tune_ops, Batch
     pl->total_blocks += pl->blocks[st];
   }
   pl->off_tune = 256;
-  pl->off_probs = pl->off_tune + tune_scratch_bytes(tune_ops, kStatBlocksBatch);
+  pl->off_probs = pl->off_tune + tune_scratch_bytes(tune_ops);
   pl->off_prefix = pl->off_probs + align256(sizeof(BatchProb) * na);
   pl->off_items = pl->off_prefix + align256(sizeof(int64_t) * (na + 1) * kB_NSTAGES);
   pl->off_owner = pl->off_items + align256(sizeof(WorkItem) * (size_t)pl->nitems);
@@ -1239,7 +1240,7 @@ int ozaki2_dgemm_batched(int batch, oz2_problem* problems, int mode, double targ
     // the phi scratch ends where this plan's tables begin
     if ((rc = get_workspace(dev, bound.total, &ws, true))) return rc;
     std::vector<double> phis;
-    if ((rc = estimate_phis(ws + bound.off_tune, srcs, kStatBlocksBatch, &phis))) return rc;
+    if ((rc = estimate_phis(ws + bound.off_tune, srcs, &phis))) return rc;
     for (size_t w = 0; w < who.size(); ++w)
       Q[who[w]].N = tune_pick_N(Q[who[w]].k, std::max(phis[2 * w], phis[2 * w + 1]),
                                 target_max_rel_err);
@@ -1288,9 +1289,9 @@ int ozaki2_estimate_phi(int64_t rows, int64_t cols, const double* X, int64_t ld,
   int dev, rc;
   if ((rc = ensure_device(&dev))) return rc;
   char* ws = nullptr;
-  if ((rc = get_workspace(dev, 256 + tune_scratch_bytes(1, kStatBlocks), &ws))) return rc;
+  if ((rc = get_workspace(dev, 256 + tune_scratch_bytes(1), &ws))) return rc;
   std::vector<double> phis;
-  if ((rc = estimate_phis(ws + 256, {stat_src(X, rows, cols, ld, vectors)}, kStatBlocks, &phis))) return rc;
+  if ((rc = estimate_phis(ws + 256, {stat_src(X, rows, cols, ld, vectors)}, &phis))) return rc;
   *phi = phis[0];
   return 0;
 }
