@@ -246,11 +246,13 @@ int get_workspace(int dev, size_t bytes, char** out, bool keeps_batch_tables = f
   return 0;
 }
 
-// Whether get_workspace (or the fixed array of ozaki2_dgemm_noalloc) can
-// supply so many bytes.
-bool workspace_fits(size_t bytes, bool fixed_ws) {
+// Whether the workspace of this call (the fixed array of
+// ozaki2_dgemm_noalloc, the caller's memory, or the library's own as it
+// stands) holds so many bytes.
+bool workspace_holds(int dev, size_t bytes, bool fixed_ws) {
   if (fixed_ws) return bytes <= (size_t)OZ2_NOALLOC_SCRATCH_BYTES;
-  return g_ws_policy == OZ2_WORKSPACE_LIBRARY || (g_user_ws && g_user_ws_bytes >= bytes);
+  if (g_user_ws && g_user_ws_bytes >= bytes) return true;
+  return g_ws_policy == OZ2_WORKSPACE_LIBRARY && g_dev[dev].ws_bytes >= bytes;
 }
 
 // Stage timing: each timed call records OZ2_NUM_STAGES + 1 events on the
@@ -442,13 +444,15 @@ int run_gemm(int64_t m, int64_t n, int64_t k, const T* A, int64_t lda, const T* 
                  : make_layout(m, n, k, N, mode, kTileBM[cfg], kTileBN[cfg]);
   // Narrow B or narrow A: conversion of the other operand, products and CRT
   // in one kernel (automatic tile choice only; a forced tile keeps the
-  // separate kernels) where its blocks fill most of the chip, or where the
-  // workspace holds only what that kernel needs (narrow B).
+  // separate kernels) where its blocks fill most of the chip, or (narrow B)
+  // where the workspace holds no more than that kernel needs: the library's
+  // own is not grown to several times the size of A for the other path.
   const bool can_fuse = !dbg && !fp8 && g_tile_policy == OZ2_TILE_AUTO && N <= kFuseMaxN &&
                         mode != OZ2_MODE_ACCURATE && k <= OZ2_K_BLOCK && HT.limbs == 2;
-  const bool fits = workspace_fits(L.total, fixed_ws);
-  const bool fused_n = can_fuse && n <= kFuseCols && (m >= kFuseMinLong || !fits);
-  const bool fused_m = can_fuse && !fused_n && m <= kFuseCols && n >= kFuseMinLong && fits;
+  const bool holds = workspace_holds(dev, L.total, fixed_ws);
+  const bool may_hold = holds || (!fixed_ws && g_ws_policy == OZ2_WORKSPACE_LIBRARY);
+  const bool fused_n = can_fuse && n <= kFuseCols && (m >= kFuseMinLong || !holds);
+  const bool fused_m = can_fuse && !fused_n && m <= kFuseCols && n >= kFuseMinLong && may_hold;
   const bool fused = fused_n || fused_m;
   if (fused) L = make_layout(m, n, k, N, mode, kFuseRows, kFuseCols, 1, fused_n, fused_m);
   char* ws = nullptr;
