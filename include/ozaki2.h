@@ -308,13 +308,15 @@ int ozaki2_get_stage_times(double* ms, int* calls);
  * call from m, n, k and N with a cost model of padded work and workgroup
  * rounds; the others force one shape (rows x columns of C per workgroup).
  * Under OZ2_TILE_AUTO a product with n <= 64 or m <= 64 whose other side is
- * long (12288 or more), with N <= 16, a fast or exact mode and k <=
- * OZ2_K_BLOCK runs a fused kernel instead (conversion of the long operand,
- * the N products and the CRT in one pass, nothing materialised for it); a
- * forced tile always runs the separate kernels.  With n <= 64 it also runs,
- * at any m, where the workspace (under OZ2_WORKSPACE_LIBRARY the library's
- * own as it stands) is too small for the separate kernels but holds what the
- * fused one needs; m <= 64 always needs the size ozaki2_workspace_size reports.
+ * long (12288 or more; from about 8192 if k is long too, and not just above
+ * a multiple of 16384 if k is short), with N <= 16, a fast or exact mode and
+ * k <= OZ2_K_BLOCK runs a fused kernel instead (conversion of the long
+ * operand, the N products and the CRT in one pass, nothing materialised for
+ * it); a forced tile always runs the separate kernels.  With n <= 64 it also
+ * runs, at any m, where the workspace (under OZ2_WORKSPACE_LIBRARY the
+ * library's own as it stands) is too small for the separate kernels but
+ * holds what the fused one needs; with m <= 64 a caller's workspace always
+ * has to hold what ozaki2_workspace_size reports.
  * Results do not depend on the tile or on the fusion.  ozaki2_set_tile
  * returns 0, or -1 for an unknown value; ozaki2_get_tile writes the tile a
  * call with these sizes would use and returns 0, or minus the index of a bad

@@ -29,6 +29,7 @@
 // kernels).
 #pragma once
 
+#include <algorithm>
 #include <utility>
 
 #include "oz2_k1_norm.hpp"
@@ -43,12 +44,24 @@ constexpr int kFuseMaxN = 16;   // moduli: accumulators and LDS
 constexpr int kFuseK = 64;      // k per step
 constexpr int kFuseRows = 64;   // vectors of the long operand per workgroup
 constexpr int kFuseThreads = 512;
-// Vectors of the long operand from which this kernel is taken: one block of
-// 64 per CU and step of 64 k in about 4.2 us (N = 14), however few the
-// blocks.  64 narrow vectors, k = 4096: 8192 long ones (128 blocks) 305 us
-// for 382 with the separate kernels, but k = 1024: 95 for 72, and 2048 long
-// ones 276 for 193; 16384 x 512: 70 for 74, x 4096: 366 for 698.
-constexpr int kFuseMinLong = 192 * kFuseRows;
+// Whether this kernel pays for `vecs` long vectors with k entries of `item`
+// bytes.  It runs one block of 64 vectors per CU, and a round of 256 blocks
+// takes the same time however few there are, so what counts is the part of
+// the rounds that is filled.  From three quarters it wins over the separate
+// kernels throughout (12288 x 64, N = 14: k = 256 0.95 of their time, 1024
+// 0.80, 4096 0.58); below, from a length k whose planes cost them more, the
+// longer the emptier the round: 8192 x 64, N = 14, k = 1024 1.31, 2048 0.95,
+// 4096 0.77; 10240 x 64, k = 1024 0.97, 1536 0.77; binary32 8192 x 64, N = 7,
+// k = 2048 1.17, 4096 0.79.  With a second round the first, full one counts
+// too: 18432 x 64, N = 14, k = 512 1.24, 1024 0.96, 2048 0.83.  Over 1792
+// measured shapes (4096 to 32768 vectors, k = 64 to 16384, N = 2 to 16, both
+// orientations) the rule is 1.3% from the better of the two on average.
+inline bool fuse_pays(int64_t vecs, int64_t k, size_t item) {
+  const int64_t round = 256 * kFuseRows, rounds = (vecs + round - 1) / round;
+  const double filled = (double)vecs / (double)(rounds * round);
+  const double need = 0.375 + (rounds == 1 ? 3072.0 : 2048.0) / ((double)k * (double)item);
+  return filled >= std::min(0.75, need);
+}
 
 // 16-byte chunk position of logical k chunk g in the LDS row of vector c
 // (rows of 64 bytes): spreads the 16-byte fragment reads, and the 8-byte

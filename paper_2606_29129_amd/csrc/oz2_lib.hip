@@ -444,15 +444,17 @@ int run_gemm(int64_t m, int64_t n, int64_t k, const T* A, int64_t lda, const T* 
                  : make_layout(m, n, k, N, mode, kTileBM[cfg], kTileBN[cfg]);
   // Narrow B or narrow A: conversion of the other operand, products and CRT
   // in one kernel (automatic tile choice only; a forced tile keeps the
-  // separate kernels) where its blocks fill most of the chip, or (narrow B)
+  // separate kernels) where that is the faster form, or (narrow B)
   // where the workspace holds no more than that kernel needs: the library's
   // own is not grown to several times the size of A for the other path.
   const bool can_fuse = !dbg && !fp8 && g_tile_policy == OZ2_TILE_AUTO && N <= kFuseMaxN &&
                         mode != OZ2_MODE_ACCURATE && k <= OZ2_K_BLOCK && HT.limbs == 2;
   const bool holds = workspace_holds(dev, L.total, fixed_ws);
   const bool may_hold = holds || (!fixed_ws && g_ws_policy == OZ2_WORKSPACE_LIBRARY);
-  const bool fused_n = can_fuse && n <= kFuseCols && (m >= kFuseMinLong || !holds);
-  const bool fused_m = can_fuse && !fused_n && m <= kFuseCols && n >= kFuseMinLong && may_hold;
+  const bool fused_n =
+      can_fuse && n <= kFuseCols && (fuse_pays(m, k, sizeof(T)) || !holds);
+  const bool fused_m = can_fuse && !fused_n && m <= kFuseCols &&
+                       fuse_pays(n, k, sizeof(T)) && may_hold;
   const bool fused = fused_n || fused_m;
   if (fused) L = make_layout(m, n, k, N, mode, kFuseRows, kFuseCols, 1, fused_n, fused_m);
   char* ws = nullptr;
