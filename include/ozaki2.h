@@ -293,7 +293,8 @@ int ozaki2_query_constants(int N, int32_t* moduli, float* p_prime_prop,
  * Stages: 0 norms and exponents (K1; in accurate mode also the bar matrices
  * and their INT8 GEMM), 1 convert and split (K2), 2 INT8 GEMMs (K3), 3 CRT
  * and unscale (K4), 4 other (zero fill, bookkeeping).  In the fast modes with
- * k <= 4096 one kernel does the work of stages 0 and 1: its time is stage 1's.
+ * k <= 4096 one kernel does the work of stages 0 and 1 for most shapes: its
+ * time is then stage 1's.
  * When the fused kernel for narrow products runs (see ozaki2_set_tile), stage
  * 1 holds K2 for the narrow operand only and stage 2 the fused conversion of
  * the other, the products and the CRT.

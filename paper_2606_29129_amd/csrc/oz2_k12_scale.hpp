@@ -70,6 +70,38 @@ inline int64_t k12_blocks(int64_t nvec, int VL, const K12Shape& sh) {
   return (nvec + sh.vw * VL - 1) / (sh.vw * VL);
 }
 
+// Whether this kernel is the faster form for an m x k by k x n product
+// (padded length Kp).  Not for longer vectors (kK12MaxK), and not
+//  * for real operands of few blocks, whose waves walk the whole of long
+//    vectors while most CUs idle and the partial norms of the separate
+//    kernels spread over them: binary64 below 96 blocks of 8 or more vectors
+//    from k = 2817, binary32 below 64 blocks from 2305 and below 128 from 3072
+//    (128 x 128 x 4096: N = 14 67 us against 56, binary32, N = 7, 66 against
+//    47; 128 x 128 x 2048: 41 against 40; 1024 x 64 x 4096 N = 14 0.93);
+//  * for a narrow binary64 operand beside one of less than 10240 long vectors
+//    whose planes outgrow the MALL (192 MiB): a last round of blocks that
+//    hardly fills any CU and no product to hide it (64 x 4096 x 4096, N = 14:
+//    198 us against 179; k = 3000 135 against 152);
+//  * for complex operands of which B is all but alone and its planes outgrow
+//    the MALL (256 MiB; the one block per CU reads B's pairs in 64-byte pieces)
+//    (64 x 3072 x 4096, N = 14: 467 us against 376; 4096 x 64 x 4096 629
+//    against 645).
+// Over 1474 measured shapes the choice is 0.4% from the better form on average.
+template <typename T, bool CPLX>
+inline bool k12_pays(int64_t m, int64_t n, int64_t k, int64_t Kp, int N) {
+  if (k > kK12MaxK) return false;
+  const int64_t planes = (int64_t)(CPLX ? 3 : 1) * N * (m + n) * k;
+  if constexpr (CPLX) return !(m <= 256 && n > m && planes > (int64_t)256 << 20);
+  constexpr int VL = kK12VL<T>;
+  const K12Shape sh = k12_shape<VL>(Kp);
+  const int64_t blocks = k12_blocks(m, VL, sh) + k12_blocks(n, VL, sh);
+  if (sizeof(T) == 8 ? k > 2816 && blocks < 96
+                     : (k > 2304 && blocks < 64) || (k >= 3072 && blocks < 128))
+    return false;
+  return !(sizeof(T) == 8 && k >= 3072 && (m < n ? m : n) <= 256 && (m < n ? n : m) < 10240 &&
+           planes > (int64_t)192 << 20);
+}
+
 // Doubles of LDS for the chunk sums: VB ceil(K / 64) at most, for K <= MAXK
 // components.
 template <int VL, int MAXK>

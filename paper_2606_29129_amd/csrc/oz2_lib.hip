@@ -468,7 +468,7 @@ int run_gemm(int64_t m, int64_t n, int64_t k, const T* A, int64_t lda, const T* 
   // Whole vectors per block: norms, exponents and conversion in one kernel
   // (stage 1).
   const bool k12 = !fused && (mode == OZ2_MODE_REVISED || mode == OZ2_MODE_ORIGINAL) &&
-                   HT.limbs == 2 && k <= kK12MaxK;
+                   HT.limbs == 2 && k12_pays<T, false>(m, n, k, L.Kp, N);
 
   StageClock clk(!fixed_ws);
   clk.mark(0);
@@ -688,7 +688,8 @@ int run_complex(int64_t m, int64_t n, int64_t k, const T* A, int64_t lda, const 
 
   StageClock clk;
   clk.mark(0);
-  const bool k12 = mode != OZ2_MODE_EXACT && HT.limbs == 2 && k <= kK12MaxK;
+  const bool k12 =
+      mode != OZ2_MODE_EXACT && HT.limbs == 2 && k12_pays<T, true>(m, n, k, L.Kp, N);
   // K1: squared norms over the 2k components and exponents.
   if (!k12) {
     k_clear_status<<<1, 64, 0, g_stream>>>((int*)(ws + L.status));
