@@ -50,17 +50,22 @@ constexpr int kFuseThreads = 512;
 // the rounds that is filled.  From three quarters it wins over the separate
 // kernels throughout (12288 x 64, N = 14: k = 256 0.95 of their time, 1024
 // 0.80, 4096 0.58); below, from a length k whose planes cost them more, the
-// longer the emptier the round: 8192 x 64, N = 14, k = 1024 1.31, 2048 0.95,
-// 4096 0.77; 10240 x 64, k = 1024 0.97, 1536 0.77; binary32 8192 x 64, N = 7,
-// k = 2048 1.17, 4096 0.79.  With a second round the first, full one counts
-// too: 18432 x 64, N = 14, k = 512 1.24, 1024 0.96, 2048 0.83.  Over 1792
+// longer the emptier the round (a single step of k is cheap from 9216 on):
+//   8192 x 64, N = 14: k = 1024 1.31, 2048 0.95, 4096 0.77; binary32, N = 7:
+//   k = 2048 1.17, 4096 0.79; 10240 x 64, N = 14: k = 1024 0.97, 1536 0.77;
+//   6144 x 64, N = 14: k = 4096 0.95, 8192 1.09.
+// With a second round the first, full one counts too: 18432 x 64, N = 14, k =
+// 512 1.24, 1024 0.96, 2048 0.83.  Two or three moduli cost the separate
+// kernels less (10240 x 64, N = 2: k = 2048 1.04, 4096 0.91).  Over 1792
 // measured shapes (4096 to 32768 vectors, k = 64 to 16384, N = 2 to 16, both
-// orientations) the rule is 1.3% from the better of the two on average.
-inline bool fuse_pays(int64_t vecs, int64_t k, size_t item) {
+// orientations) the rule is 0.9% from the better of the two on average.
+inline bool fuse_pays(int64_t vecs, int64_t k, size_t item, int N) {
   const int64_t round = 256 * kFuseRows, rounds = (vecs + round - 1) / round;
   const double filled = (double)vecs / (double)(rounds * round);
-  const double need = 0.375 + (rounds == 1 ? 3072.0 : 2048.0) / ((double)k * (double)item);
-  return filled >= std::min(0.75, need);
+  if (k <= kFuseK) return filled >= 0.5625;
+  const double per_byte = (N < 4 ? 2.0 : 1.0) / ((double)k * (double)item);
+  const double need = rounds == 1 ? 0.25 + 4096.0 * per_byte : 0.375 + 1536.0 * per_byte;
+  return filled >= std::min(0.75, std::max(0.4375, need));
 }
 
 // 16-byte chunk position of logical k chunk g in the LDS row of vector c

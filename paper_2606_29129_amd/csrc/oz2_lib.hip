@@ -452,9 +452,9 @@ int run_gemm(int64_t m, int64_t n, int64_t k, const T* A, int64_t lda, const T* 
   const bool holds = workspace_holds(dev, L.total, fixed_ws);
   const bool may_hold = holds || (!fixed_ws && g_ws_policy == OZ2_WORKSPACE_LIBRARY);
   const bool fused_n =
-      can_fuse && n <= kFuseCols && (fuse_pays(m, k, sizeof(T)) || !holds);
+      can_fuse && n <= kFuseCols && (fuse_pays(m, k, sizeof(T), N) || !holds);
   const bool fused_m = can_fuse && !fused_n && m <= kFuseCols &&
-                       fuse_pays(n, k, sizeof(T)) && may_hold;
+                       fuse_pays(n, k, sizeof(T), N) && may_hold;
   const bool fused = fused_n || fused_m;
   if (fused) L = make_layout(m, n, k, N, mode, kFuseRows, kFuseCols, 1, fused_n, fused_m);
   char* ws = nullptr;

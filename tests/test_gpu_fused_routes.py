@@ -23,7 +23,10 @@ DEV = "cuda:0"
     (10240, 1536, "float64", True), (12287, 256, "float64", False),
     (12288, 256, "float64", True), (16384, 64, "float64", True),
     (18432, 512, "float64", False), (18432, 2048, "float64", True),
-    (20480, 1024, "float64", True), (24576, 64, "float64", True)])
+    (20480, 1024, "float64", True), (24576, 64, "float64", True),
+    (9216, 64, "float64", True), (9215, 64, "float64", False), (18432, 1024, "float64", True),
+    (18432, 2048, "float32", True), (8192, 4096, "float32", True),
+    (7168, 4096, "float64", True), (7100, 16384, "float64", False)])
 def test_route(long, k, dtype, fused, across):
     """The separate kernels fill the residue planes of both operands; the
     fused one writes nothing in the upper half of their workspace."""
