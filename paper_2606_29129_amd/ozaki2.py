@@ -283,7 +283,12 @@ def ensure_workspace(nbytes, device=None):
     never allocates device memory (its default workspace policy); this is
     where the conveniences below get theirs.  Returns the address."""
     import torch
-    idx = None if device is None else torch.device(device).index
+    idx = None
+    if device is not None:
+        device = torch.device(device)
+        if device.type != "cuda":
+            raise ValueError(f"expected a cuda device, got {device}")
+        idx = device.index
     if idx is None:
         idx = torch.cuda.current_device()
     cur = _workspaces.get(idx)
