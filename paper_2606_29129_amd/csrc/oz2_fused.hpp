@@ -24,9 +24,13 @@
 // Two waves per SIMD (at most 128 accumulators each) rather than one with all
 // moduli of 16 vectors: alone on its SIMD a wave issues an operation at best
 // every 5.3 cycles, and a dependent binary64 one every 11 (two waves: 5.9).
-// 65536 x 64 x 4096, N = 14: 1.05 ms (1.28 with one wave per SIMD), 2.15 GB
-// read at 2.0 TB/s; the transposed shape 1.00 ms (2.0 ms in the separate
-// kernels).
+// 65536 x 64 x 4096, N = 14: 1.06 ms (1.28 with one wave per SIMD), 2.15 GB
+// read at 2.0 TB/s; the transposed shape 1.07 ms (2.0 ms in the separate
+// kernels).  At N = 15 and 16 the accumulators leave too few registers: up to
+// 18 dwords per lane spill at N = 15 and 5 at N = 16 (strided operand), none
+// below.  With two moduli the loads are the bound, and one step of them in
+// flight is little: the whole 12288 x 64 x 4096 call takes 196 us, 180 with the
+// kernel of one wave per SIMD (N = 3: 1.03 at most; from 4 on faster).
 #pragma once
 
 #include <algorithm>
@@ -292,7 +296,8 @@ __global__ __launch_bounds__(kFuseThreads, 2) void k234_fused(
       __builtin_amdgcn_sched_barrier(0);   // one plane at a time (registers)
     });
     // the narrow operand's slab of this step has landed (the next entries of
-    // the long one may still be on their way)
+    // the long one may still be on their way; binary32 ones are waited for
+    // where they are converted, behind their loads)
     if (s + 1 < nsteps) wait_vmem_n_lds_all<kXLoads>();
     else wait_vmem_lds_all();
     __syncthreads();

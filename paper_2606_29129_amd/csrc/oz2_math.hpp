@@ -108,7 +108,9 @@ OZ2_HD float rd_f32(double d) {
 // from round-to-nearest operations and their exact errors.  The operations
 // are volatile asm, which keeps them in order between the two mode switches;
 // round_up_end takes the sum so that what is computed from it (in
-// round-to-nearest) stays behind the switch back.
+// round-to-nearest) stays behind the switch back.  ru_square, ru_add and
+// ru_add_squares round up only between the two (elsewhere to nearest), and
+// only on the device.
 __device__ __forceinline__ void round_up_begin() {
 #if defined(__HIP_DEVICE_COMPILE__)
   asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 2, 2), 1");
