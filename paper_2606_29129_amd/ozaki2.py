@@ -285,7 +285,8 @@ def ensure_workspace(nbytes, device=None):
     import torch
     idx = None
     if device is not None:
-        device = torch.device(device)
+        if not isinstance(device, torch.device):
+            device = torch.device(device)
         if device.type != "cuda":
             raise ValueError(f"expected a cuda device, got {device}")
         idx = device.index
