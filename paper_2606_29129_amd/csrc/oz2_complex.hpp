@@ -304,6 +304,8 @@ __global__ __launch_bounds__(256) void k4_crt_cplx(
 #pragma unroll
       for (int q = 0; q < RW; ++q) w[c][q] = nx[c][q];
   }
+  // In the loop, not behind a branch of its own as in the real kernel: there it
+  // took 15 registers and a wave per SIMD (2000 x 2000 outputs 1.5% of the call).
   bool bad = bi == 0 && f == kExpNonFinite;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
@@ -324,17 +326,16 @@ __global__ __launch_bounds__(256) void k4_crt_cplx(
           b[s] = ai[r][s];
         }
         if constexpr (sizeof(TO) == 8) {
-          out.x = crt_unscale<S, 53, -1074>(a, T, e + f);
-          out.y = crt_unscale<S, 53, -1074>(b, T, e + f);
+          out.x = crt_unscale<S, 53, -1074, true>(a, T, e + f);
+          out.y = crt_unscale<S, 53, -1074, true>(b, T, e + f);
         } else {
-          out.x = (TO)crt_unscale<S, 24, -149>(a, T, e + f);
-          out.y = (TO)crt_unscale<S, 24, -149>(b, T, e + f);
+          out.x = (TO)crt_unscale<S, 24, -149, true>(a, T, e + f);
+          out.y = (TO)crt_unscale<S, 24, -149, true>(b, T, e + f);
         }
       }
     }
     tile[wave][lr - RPW * h][lc] = out;
   }
-  k4_set_status(status, bad);
   // LDS operations of one wave complete in order; the fence keeps the
   // compiler from moving the reads above the writes.
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -348,6 +349,7 @@ __global__ __launch_bounds__(256) void k4_crt_cplx(
     const int64_t c = bj * 32 + oc;
     if (row < m && c < n) C2[row + c * ldc] = tile[wave][orow][oc];
   }
+  k4_set_status(status, bad);
 }
 
 }  // namespace oz2

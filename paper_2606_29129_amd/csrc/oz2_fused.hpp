@@ -362,8 +362,8 @@ __global__ __launch_bounds__(kFuseThreads, 2) void k234_fused(
       const int32_t e = eX[x], f = eW[wi];
       double v;
       if (e == kExpNonFinite || f == kExpNonFinite) v = __builtin_nan("");
-      else if constexpr (sizeof(TO) == 8) v = crt_unscale<S, 53, -1074>(sums[j], TB, e + f);
-      else v = crt_unscale<S, 24, -149>(sums[j], TB, e + f);
+      else if constexpr (sizeof(TO) == 8) v = crt_unscale<S, 53, -1074, true>(sums[j], TB, e + f);
+      else v = crt_unscale<S, 24, -149, true>(sums[j], TB, e + f);
       C[CONTIG ? wi + x * ldc : x + wi * ldc] = (TO)v;
     }
   }

@@ -203,8 +203,9 @@ OZ2_HD double round_signed(const double (&D)[S], int32_t E) {
 }
 
 // PREC = 53 (binary64) or 24 (binary32); EMIN_Q = exponent of the smallest
-// subnormal (-1074 or -149).
-template <int S, int PREC, int EMIN_Q>
+// subnormal (-1074 or -149).  S is at least the table's slice count; OWN: it is
+// the table's own.
+template <int S, int PREC, int EMIN_Q, bool OWN = false>
 OZ2_HD double crt_unscale(const double (&acc)[S], const ModTable& T, int32_t E) {
   // Quotient estimate and the exact residual R = X - Q P (|R_s| < 2^52:
   // |Acc_s| < 2^51 and |Q P_s| < 2^51).
@@ -212,27 +213,36 @@ OZ2_HD double crt_unscale(const double (&acc)[S], const ModTable& T, int32_t E) 
   double R[S];
 #pragma unroll
   for (int s = 0; s < S; ++s) R[s] = fma(-Q, T.P[s], acc[s]);
-  // The rounded value r of R is within a factor 1 +- 2^-50 of R, so |r| <=
-  // halfP (P/2 (1 - 2^-30)) proves |R| < P/2, i.e. R = C''.  (All S slices
-  // count: a kernel whose S exceeds the table's own slice count, such as the
-  // batch's, makes the same decision.)  The bound is as near to P/2 as that
-  // allows: where k is 1 the scaling puts most |C''| between P/8 and P/2, and
-  // with P/4 a wave took both paths (binary32 8192 x 8192, k = 1, N = 7, whole
-  // call: 504 us, 366 now; binary64, N = 14: 773, 666).
-  double r = slices_value(R);
-  // The common case, about 40 operations against 80 below: R is C'' without a
-  // doubt and the result is normal (|C''| >= 1, or 0, puts |C| above 2^-E).
-  // (8192 x 8192 outputs, N = 14: 380 -> 340 us, 1.48 GB at 4.3 TB/s, near a
-  // plain copy's 4.6; 16384 x 16384, N = 17: 1.75 -> 1.70 ms; complex 4096 x
-  // 4096 402 -> 378 us.)
+  // Is |R| < P/2, i.e. R = C'', without a doubt?  The rounded value r of R is
+  // within a factor 1 +- 2^-50 of R, so |r| <= halfP (P/2 (1 - 2^-30)) proves
+  // it, whatever part of the S slices the table fills.  Where it fills them all
+  // the top two are enough: h = R_{S-1} 2^39 + R_{S-2} is R in units of 2^(39
+  // (S-2)) within 2^14 + 1 and a rounding, so |h| <= fastH does (in fewer
+  // operations: 64 x 4096 outputs, N = 14, 7.7 -> 7.3 us).  The bounds are as
+  // near to P/2 as that allows: where k is 1 the scaling puts most |C''| between
+  // P/8 and P/2, and with P/4 a wave took both paths (binary32 8192 x 8192, k =
+  // 1, N = 7, whole call: 504 us, 366 now; binary64, N = 14: 773, 666).
+  double r = 0.0;
+  bool sure = false;
+  if constexpr (OWN && S >= 2) {
+    sure = fabs(fma(R[S - 1], sconst(0x1p39), R[S - 2])) <= T.fastH;
+  } else {
+    r = slices_value(R);
+    sure = fabs(r) <= T.halfP;
+  }
+  // The common case, about 40 operations against 80 below: R is C'' and the
+  // result is normal (|C''| >= 1, or 0, puts |C| above 2^-E).  (8192 x 8192
+  // outputs, N = 14: 380 -> 340 us, 1.48 GB at 4.3 TB/s, near a plain copy's 4.6;
+  // 16384 x 16384, N = 17: 1.75 -> 1.70 ms; complex 4096 x 4096 402 -> 378 us.)
   if constexpr (S >= 2) {
-    if (fabs(r) <= T.halfP && E <= -(EMIN_Q + PREC - 1)) {
+    if (sure && E <= -(EMIN_Q + PREC - 1)) {
       normalize(R);
       return round_signed<S, PREC>(R, E);
     }
   }
   // Bring R into (-P/2, P/2): R = C'' + jP with |j| <= 1 and |C''| < P/2.
-  // Where r leaves a doubt the exact comparisons with P/2 decide.
+  // Where there is a doubt the exact comparisons with P/2 decide.
+  if constexpr (OWN && S >= 2) r = slices_value(R);
   if (!(fabs(r) <= T.halfP)) {
     double D[S];
 #pragma unroll
@@ -294,7 +304,8 @@ __device__ __forceinline__ void k4_set_status(int* __restrict__ status, bool bad
 constexpr int kK4WavesPerBlock = 2;
 constexpr int kK4WavesPerBlockSmall = 4;
 
-template <int S, typename TO, int WPB = kK4WavesPerBlock>
+// OWN: see crt_unscale.
+template <int S, typename TO, int WPB = kK4WavesPerBlock, bool OWN = false>
 __device__ __forceinline__ void k4_crt_body(
     const uint8_t* __restrict__ U, const int32_t* __restrict__ eA,
     const int32_t* __restrict__ eB, const ModTable* __restrict__ tab, int N,
@@ -372,7 +383,12 @@ __device__ __forceinline__ void k4_crt_body(
 #pragma unroll
       for (int q = 0; q < RW; ++q) cur[i][q] = nxt[i][q];
   }
-  bool bad = bi == 0 && f == kExpNonFinite;
+  if (status && (bi == 0 || bj == 0)) {   // a scalar branch elsewhere
+    bool bad = bi == 0 && f == kExpNonFinite;
+#pragma unroll
+    for (int r = 0; r < R; ++r) bad = bad || (bj == 0 && er[r] == kExpNonFinite);
+    k4_set_status(status, bad);
+  }
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int lr = acc_row(R * h + r, lane);     // RPW h .. RPW h + RPW - 1
@@ -380,20 +396,18 @@ __device__ __forceinline__ void k4_crt_body(
     double v = 0.0;
     if (row < m && col < n) {
       const int32_t e = er[r];
-      bad = bad || (bj == 0 && e == kExpNonFinite);
       if (e == kExpNonFinite || f == kExpNonFinite) {
         v = __builtin_nan("");
       } else {
         double a[S];
 #pragma unroll
         for (int s = 0; s < S; ++s) a[s] = acc[r][s];
-        if constexpr (sizeof(TO) == 8) v = crt_unscale<S, 53, -1074>(a, T, e + f);
-        else v = crt_unscale<S, 24, -149>(a, T, e + f);
+        if constexpr (sizeof(TO) == 8) v = crt_unscale<S, 53, -1074, OWN>(a, T, e + f);
+        else v = crt_unscale<S, 24, -149, OWN>(a, T, e + f);
       }
     }
     tile[wave][lr - RPW * h][lc] = (TO)v;
   }
-  k4_set_status(status, bad);
   // LDS operations of one wave complete in order; the fence keeps the
   // compiler from moving the reads above the writes.
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -415,7 +429,7 @@ __global__ __launch_bounds__(256) void k4_crt(
     const int32_t* __restrict__ eB, const ModTable* __restrict__ tab, int N,
     int64_t m, int64_t n, int64_t Mp, int64_t Np, TO* __restrict__ C, int64_t ldc,
     int* __restrict__ status) {
-  k4_crt_body<S, TO, WPB>(U, eA, eB, tab, N, m, n, Mp, Np, C, ldc, blockIdx.x, status);
+  k4_crt_body<S, TO, WPB, true>(U, eA, eB, tab, N, m, n, Mp, Np, C, ldc, blockIdx.x, status);
 }
 
 // C = 0 (k = 0).

@@ -32,6 +32,7 @@ struct ModTable {
   double H[kMaxSlices];            // P/2 in 39-bit slices
   double invP;                     // RN(1/P), only for quotient estimates
   double halfP;                    // a binary64 value a little below P/2
+  double fastH;                    // halfP in units of 2^(39 (slices - 2)), less 2^15
   double pm1_rd;                   // RD64(P - 1): x <= P - 1 iff x <= pm1_rd (binary64 x)
   float p_prop;                    // P'_prop = RD32(log2(P-1)/2 - 0.5)
   float p_fast;                    // P'_fast = RD32(log2(P-1)/2 - 1.5)
@@ -178,6 +179,7 @@ inline bool build_table(int N, bool accurate_limbs, ModTable* T) {
   T->log2P = (double)log2P;
   T->invP = (double)exp2l(-log2P);
   T->halfP = (double)(exp2l(log2P - 1.0L) * (1.0L - 0x1p-30L));
+  T->fastH = ldexp(T->halfP, -kSliceBits * (T->slices - 2)) - 0x1p15;
   {
     // P - 1 rounded down to binary64: its top 53 bits, truncated.
     const Big Pm1 = P.sub_small(1);
