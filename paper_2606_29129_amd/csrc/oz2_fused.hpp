@@ -101,16 +101,23 @@ constexpr double kFuseMagic = 0x1.8p52;
 // 8 bytes per lane to LDS address a + off.  As asm, since the compiler
 // cannot tell these writes from the direct global->LDS loads in flight to
 // the other array and would wait for them first; the caller waits (lgkmcnt)
-// before the barrier.  It starts on 8 bytes, and with it most of the
-// conversion's instructions, five in six of which are 8 bytes long: left to
-// chance (385 of 551 off by 4 in one build) the kernel took 2% more (65536 x
-// 64 x 4096, N = 14, transposed: 1090 us, 1068 now).
-template <int OFF>
+// before the barrier.  It fixes the place of the code behind it, five in six of
+// whose instructions are 8 bytes long: left to chance (385 of 551 off by 4 in
+// one build) the kernel took 2% more.  With two limbs a plane's code has an even
+// number of 4-byte instructions up to its first long run, with one limb an odd
+// one, hence the s_nop (65536 x 64 x 2048: N = 13 648 us without it, 629 with;
+// N = 14, transposed, x 4096 1090 -> 1068).
+template <int OFF, int LIMBS>
 __device__ __forceinline__ void lds_write8(uint32_t a, uint32_t lo, uint32_t hi) {
 #if defined(__HIP_DEVICE_COMPILE__)
   typedef uint32_t u2 __attribute__((ext_vector_type(2)));
   const u2 w = {lo, hi};
-  asm volatile(".p2align 3\n\tds_write_b64 %0, %1 offset:%2" ::"v"(a), "v"(w), "n"(OFF) : "memory");
+  if constexpr (LIMBS == 1)
+    asm volatile(".p2align 3\n\ts_nop 0\n\tds_write_b64 %0, %1 offset:%2" ::"v"(a), "v"(w), "n"(OFF)
+                 : "memory");
+  else
+    asm volatile(".p2align 3\n\tds_write_b64 %0, %1 offset:%2" ::"v"(a), "v"(w), "n"(OFF)
+                 : "memory");
 #endif
 }
 // The value is computed here, not later.
@@ -288,11 +295,12 @@ __global__ __launch_bounds__(kFuseThreads, 2) void k234_fused(
     if (s + 1 < nsteps) load_x(k0 + kFuseK);
     fuse_for<NP>([&](auto tc) {
       constexpr int t = decltype(tc)::value;
-      lds_write8<t * PB>(xdst,
-                         pack_low_bytes(fuse_residue<t>(L[0]), fuse_residue<t>(L[1]),
-                                        fuse_residue<t>(L[2]), fuse_residue<t>(L[3])),
-                         pack_low_bytes(fuse_residue<t>(L[4]), fuse_residue<t>(L[5]),
-                                        fuse_residue<t>(L[6]), fuse_residue<t>(L[7])));
+      lds_write8<t * PB, LIMBS>(
+          xdst,
+          pack_low_bytes(fuse_residue<t>(L[0]), fuse_residue<t>(L[1]), fuse_residue<t>(L[2]),
+                         fuse_residue<t>(L[3])),
+          pack_low_bytes(fuse_residue<t>(L[4]), fuse_residue<t>(L[5]), fuse_residue<t>(L[6]),
+                         fuse_residue<t>(L[7])));
       __builtin_amdgcn_sched_barrier(0);   // one plane at a time (registers)
     });
     // the narrow operand's slab of this step has landed (the next entries of
