@@ -70,8 +70,12 @@ inline int64_t k12_blocks(int64_t nvec, int VL, const K12Shape& sh) {
   return (nvec + sh.vw * VL - 1) / (sh.vw * VL);
 }
 
+// Most blocks of a launch: it holds fewer than 2^32 work-items.
+constexpr int64_t kK12MaxBlocks = (int64_t(1) << 32) / (64 * kK12Waves);
+
 // Whether this kernel is the faster form for an m x k by k x n product
-// (padded length Kp).  Not for longer vectors (kK12MaxK), and not
+// (padded length Kp).  Not for longer vectors (kK12MaxK), nor for more blocks
+// than a launch takes, and not
 //  * for real operands of few blocks, whose waves walk the whole of long
 //    vectors while most CUs idle and the partial norms of the separate
 //    kernels spread over them: binary64 below 96 blocks of 8 or more vectors
@@ -90,11 +94,12 @@ inline int64_t k12_blocks(int64_t nvec, int VL, const K12Shape& sh) {
 template <typename T, bool CPLX>
 inline bool k12_pays(int64_t m, int64_t n, int64_t k, int64_t Kp, int N) {
   if (k > kK12MaxK) return false;
+  constexpr int VL = CPLX ? kK12VLCplx : kK12VL<T>;
+  const K12Shape sh = k12_shape<VL>(CPLX ? 2 * Kp : Kp);
+  const int64_t blocks = k12_blocks(m, VL, sh) + k12_blocks(n, VL, sh);
+  if (blocks >= kK12MaxBlocks) return false;
   const int64_t planes = (int64_t)(CPLX ? 3 : 1) * N * (m + n) * k;
   if constexpr (CPLX) return !(m <= 256 && n > m && planes > (int64_t)256 << 20);
-  constexpr int VL = kK12VL<T>;
-  const K12Shape sh = k12_shape<VL>(Kp);
-  const int64_t blocks = k12_blocks(m, VL, sh) + k12_blocks(n, VL, sh);
   if (sizeof(T) == 8 ? k > 2816 && blocks < 96
                      : (k > 2304 && blocks < 64) || (k >= 3072 && blocks < 128))
     return false;

@@ -899,12 +899,19 @@ int plan_batch(int batch, const oz2_problem* P, int mode, size_t tune_ops, Batch
   }
   if (pl->nitems > INT32_MAX) return OZ2_ERR_TOO_LARGE;
   pl->prefix.assign((size_t)(na + 1) * kB_NSTAGES, 0);
+  int64_t k12_total = 0;
+  for (int a = 0; a < na; ++a) {
+    const oz2_problem& q = P[pl->act[a]];
+    const K12Shape sh = k12_shape<kK12VL<double>>(pl->lay[a].Kp);
+    if (q.k <= kK12MaxK)
+      k12_total += k12_blocks(q.m, kK12VL<double>, sh) + k12_blocks(q.n, kK12VL<double>, sh);
+  }
   for (int st = 0; st < kB_NSTAGES; ++st) {
     int64_t acc = 0;
     for (int a = 0; a < na; ++a) {
       const oz2_problem& q = P[pl->act[a]];
       const Layout& L = pl->lay[a];
-      const bool k12 = q.k <= kK12MaxK;
+      const bool k12 = q.k <= kK12MaxK && k12_total < kK12MaxBlocks;
       const K12Shape sh = k12_shape<kK12VL<double>>(L.Kp);
       int64_t c = 0;
       switch (st) {
